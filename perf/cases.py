@@ -280,10 +280,10 @@ def work(case):
 def tolerance(case):
     """Cache rows and kept tokens are copies and whole numbers.  Attention outputs, measured against 64 bits: bf16 results
     with bf16 or fp32 probabilities 1.7e-3 to 2.2e-3 (largest single difference 0.013 of the root mean square), of which
-    the rounding of the result alone is 1.7e-3; fp32 caches 3e-7 to 6e-7.  About four times that."""
+    the rounding of the result alone is 1.7e-3; fp32 caches 2.7e-7 to 4.5e-7 (largest 5e-6).  About four times that."""
     if case["kind"] == "compress":
         return "exact"
-    return {"rel": 2e-6, "max": 1e-5} if case["kv"] == "f32" else {"rel": 8e-3, "max": 0.05}
+    return {"rel": 2e-6, "max": 2e-5} if case["kv"] == "f32" else {"rel": 8e-3, "max": 0.05}
 
 
 # ------------------------------------------------------------------------------------------------ exact values
