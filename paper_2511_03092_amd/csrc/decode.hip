@@ -7,12 +7,14 @@
 //   decode_mfma    per (chunk, sequence, KV head), one wave: bf16 MFMA
 //                  K x q^T for the G heads of the group (padded to 16 columns),
 //                  online softmax in the exp2 domain, MFMA V^T x P^T; bf16 or
-//                  fp8 E4M3 rows (converted to bf16 in registers)
+//                  fp8 E4M3 rows (converted to bf16 in registers), 64 or 128
+//                  wide, with a V cache or with the values in the key rows
 //   decode_mla_lds bf16 latent rows (576 wide, values = first 512 dims): four
 //                  waves per (chunk, sequence) streaming 32-row blocks through
 //                  a 4-stage LDS ring
 //   decode_mla     fp8 latent rows, register-streamed
-//   decode_generic one wave per (chunk, sequence, query head); any dtype
+//   decode_generic one wave per (chunk, sequence, query head): fp32 caches and
+//                  latent caches of several KV heads
 //   combine        log-sum-exp merge of the chunk partials -> out
 // decode_mfma (bf16 and fp8 caches) and decode_mla_lds (bf16) also take the
 // new token (snap_decode_step): the append happens in the same launch.
@@ -41,7 +43,7 @@ struct DecodeArgs {
   const int32_t* slot_ids;
   float* part;           // [n][Hq][n_chunks][dv]
   float2* ml;            // [n][Hq][n_chunks]  (max in log2 units, sum)
-  // fused append (bf16 caches only): the token at pos, [n][Hkv][dk] / [n][Hkv][dv];
+  // fused append: the token at pos, [n][Hkv][dk] / [n][Hkv][dv];
   // NULL when the launch only attends
   const void* k_new;
   const void* v_new;
@@ -101,18 +103,14 @@ __device__ __forceinline__ u32x4 e4m3x8_to_bf16x8(u32x2 c) {
 // with the bf16 K chunk order of decode_mfma (kchunk), 7% for the bf16 one;
 // on a one-layer 32k call (17 MB, re-read from that cache every step) it
 // was slower, so small calls load without it.
-template <bool FP8>
-struct Raw8 {
-  typedef u32x4 T;
-};
-template <>
-struct Raw8<true> {
-  typedef u32x2 T;
+template <bool FP8, int E = 8>
+struct Raw {  // E elements of one row
+  typedef uint32_t T __attribute__((ext_vector_type(E / (FP8 ? 4 : 2))));
 };
 
-template <bool FP8, bool NT>
-__device__ __forceinline__ typename Raw8<FP8>::T load_raw8(const void* base, size_t elem, bool ok) {
-  typedef typename Raw8<FP8>::T T;
+template <bool FP8, bool NT, int E = 8>
+__device__ __forceinline__ typename Raw<FP8, E>::T load_raw(const void* base, size_t elem, bool ok) {
+  typedef typename Raw<FP8, E>::T T;
   T z = {};
   if (!ok) return z;
   const T* p = FP8 ? (const T*)((const uint8_t*)base + elem) : (const T*)((const uint16_t*)base + elem);
@@ -122,12 +120,22 @@ __device__ __forceinline__ typename Raw8<FP8>::T load_raw8(const void* base, siz
     return *p;
 }
 
-template <bool FP8>
-__device__ __forceinline__ u32x4 bf16x8_of(typename Raw8<FP8>::T r) {
-  if constexpr (FP8)
-    return e4m3x8_to_bf16x8(r);
-  else
+// raw elements as packed bf16 pairs
+template <bool FP8, int E = 8>
+__device__ __forceinline__ typename Raw<false, E>::T bf16_of(typename Raw<FP8, E>::T r) {
+  if constexpr (!FP8) {
     return r;
+  } else if constexpr (E == 8) {
+    return e4m3x8_to_bf16x8(r);
+  } else {
+    typename Raw<false, E>::T o;
+#pragma unroll
+    for (int i = 0; i < E / 4; ++i) {
+      o[2 * i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[i], 1.0f, false));
+      o[2 * i + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[i], 1.0f, true));
+    }
+    return o;
+  }
 }
 
 // 8 bf16 values (low half of each word first) -> the 8 E4M3 codes of
@@ -152,7 +160,7 @@ __device__ __forceinline__ u32x2 bf16x8_to_e4m3x8(u32x4 raw, float scale) {
 // raw form: bf16 as is, fp8 quantised with the slot's scale (the bytes the
 // append writes, so attending them equals attending the appended row).
 template <bool FP8>
-__device__ __forceinline__ typename Raw8<FP8>::T new_raw8(const void* src, size_t elem, float scale) {
+__device__ __forceinline__ typename Raw<FP8>::T new_raw8(const void* src, size_t elem, float scale) {
   const u32x4 raw = *(const u32x4*)((const uint16_t*)src + elem);
   if constexpr (FP8)
     return bf16x8_to_e4m3x8(raw, scale);
@@ -199,9 +207,20 @@ __device__ __forceinline__ void new_piece_store(const DecodeArgs& a, int g, int 
 }
 
 // ---------------------------------------------------------------- MFMA decode
-// KSTEPS = dk / 32, VPASS = dv / 128.  Lane l owns head l%16 of the group and,
-// per 16-row set, the output rows 4*(l/16)+e; P never leaves the lane between
-// the two products because the V operand is loaded in the matching row order.
+// KSTEPS = d / 32 (key and value rows are both d wide: 64 or 128).  Lane l
+// owns head l%16 of the group and, per 16-row set, the output rows 4*(l/16)+e;
+// P never leaves the lane between the two products because the V operand is
+// loaded in the matching row order (d / 16 consecutive dims of eight rows per
+// lane).
+// PARTS: how many bf16 terms the probabilities are split into for the value
+// product.  1: rounded to bf16 (separate K and V caches of 128-wide rows).
+// 3: p = p1 + p2 + p3 (24 bits), for the shapes whose probabilities
+// are held in 32 bits: 64-wide rows and caches whose values are the key rows.
+// The two further products per 16 dims cost nothing there: a 32-row block is
+// 8 KB of 64-wide bf16 rows against 16 matrix instructions.  HBM bound: 64-wide
+// bf16, 32 sequences x 8 KV heads x 16384 rows, 2916 -> 162 us a call (6.6
+// TB/s) from one wave per query head on decode_generic; 8 x 4096 rows 172 -> 18
+// us; fp32 results 3e-7 to 6e-7 from 64 bits (2e-7 to 1e-6 before).
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 // The 8-element chunk of a 32 * KSTEPS-wide row that lane group lg feeds to
@@ -216,11 +235,13 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 template <int KSTEPS, bool FP8, bool NT>
 __device__ __forceinline__ int kchunk(int t, int lg) { return (FP8 || !NT) ? KSTEPS * lg + t : 4 * t + lg; }
 
-template <int KSTEPS, int VPASS, bool FP8, bool QK8, bool NT>
+template <int KSTEPS, int PARTS, bool FP8, bool QK8, bool NT>
 __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
   static_assert(!QK8 || (FP8 && KSTEPS == 4), "fp8 products need an fp8 cache of 128-wide rows");
   constexpr int D = KSTEPS * 32;
-  typedef typename Raw8<FP8>::T RawT;
+  constexpr int VE = D / 16;  // value dims per lane
+  typedef typename Raw<FP8>::T RawT;
+  typedef typename Raw<FP8, VE>::T RawV;
   const int lane = tid(), l16 = lane & 15, lg = lane >> 4;
   const int chunk = bid_x(), bg = bid_y(), b = bg / a.Hkv, g = bg % a.Hkv;
   int slot;
@@ -279,25 +300,23 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
   // fp8: the chunk that attends the new row quantises it once into LDS (K
   // codes in pieces [0, D/8), V codes after them, 8 codes per piece) and
   // stores those codes into the cache at its end
-  __shared__ u32x2 newq[FP8 ? (D + 128 * VPASS) / 8 : 1];
+  __shared__ u32x2 newq[FP8 ? 2 * D / 8 : 1];
   const bool owns_new = FP8 && vnew >= sp.v0 && vnew < sp.v1;
   if constexpr (FP8) {
     if (owns_new) {
       constexpr int kc = D / 8;
       if (lane < kc)
         newq[lane] = new_raw8<true>(a.k_new, knew_off + 8 * lane, ksc);
-      else if (lane < kc + 16 * VPASS)
+      else if (lane < 2 * kc)
         newq[lane] = new_raw8<true>(a.v_new, vnew_off + 8 * (lane - kc), vsc);
       __syncthreads();
     }
   }
 
   float m = -INFINITY, mref = 0.f, lsum = 0.f;  // reference max (log2 units), its finite stand-in, sum
-  f32x4 acc[VPASS][8];
+  f32x4 acc[VE];
 #pragma unroll
-  for (int pp = 0; pp < VPASS; ++pp)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[pp][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < VE; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // a whole block inside one run of the row map, without the new token: 32
   // consecutive cache rows from a uniform base (wave-uniform test)
@@ -311,8 +330,8 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
 #pragma unroll
       for (int t = 0; t < KSTEPS; ++t) {
         const int col = 8 * kchunk<KSTEPS, FP8, NT>(t, lg);
-        ka[t] = load_raw8<FP8, NT>(a.ck, e0 + col, true);
-        kb[t] = load_raw8<FP8, NT>(a.ck, e0 + 16 * D + col, true);
+        ka[t] = load_raw<FP8, NT>(a.ck, e0 + col, true);
+        kb[t] = load_raw<FP8, NT>(a.ck, e0 + 16 * D + col, true);
       }
       return;
     }
@@ -323,11 +342,11 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
     for (int t = 0; t < KSTEPS; ++t) {
       const int col = 8 * kchunk<KSTEPS, FP8, NT>(t, lg);
       if constexpr (FP8) {
-        ka[t] = va == vnew ? newq[col / 8] : load_raw8<FP8, NT>(a.ck, ea + col, va < sp.v1);
-        kb[t] = vb2 == vnew ? newq[col / 8] : load_raw8<FP8, NT>(a.ck, eb + col, vb2 < sp.v1);
+        ka[t] = va == vnew ? newq[col / 8] : load_raw<FP8, NT>(a.ck, ea + col, va < sp.v1);
+        kb[t] = vb2 == vnew ? newq[col / 8] : load_raw<FP8, NT>(a.ck, eb + col, vb2 < sp.v1);
       } else {
-        ka[t] = load_raw8<FP8, NT>(va == vnew ? a.k_new : a.ck, va == vnew ? knew_off + col : ea + col, va < sp.v1);
-        kb[t] = load_raw8<FP8, NT>(vb2 == vnew ? a.k_new : a.ck, vb2 == vnew ? knew_off + col : eb + col, vb2 < sp.v1);
+        ka[t] = load_raw<FP8, NT>(va == vnew ? a.k_new : a.ck, va == vnew ? knew_off + col : ea + col, va < sp.v1);
+        kb[t] = load_raw<FP8, NT>(vb2 == vnew ? a.k_new : a.ck, vb2 == vnew ? knew_off + col : eb + col, vb2 < sp.v1);
       }
     }
   };
@@ -337,28 +356,25 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
   for (int vb = sp.v0; vb < sp.v1; vb += 32) {
     // V of this block (eight rows per lane, in the order of the score layout),
     // then K of the next block: the value product waits only for V.
-    RawT vv[VPASS][8];
+    RawV vv[8];
     if (plain(vb)) {
-      const size_t e0 = (row0 + virt_row(vb, sp.n1, sr)) * vstride + 8 * l16;
+      const size_t e0 = (row0 + virt_row(vb, sp.n1, sr)) * vstride + VE * l16;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int r = i < 4 ? 4 * lg + i : 16 + 4 * lg + (i - 4);
-#pragma unroll
-        for (int pp = 0; pp < VPASS; ++pp) vv[pp][i] = load_raw8<FP8, NT>(vbase, e0 + (size_t)r * vstride + 128 * pp, true);
+        vv[i] = load_raw<FP8, NT, VE>(vbase, e0 + (size_t)r * vstride, true);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int vi = vb + (i < 4 ? 4 * lg + i : 16 + 4 * lg + (i - 4));
         const size_t ev = (row0 + virt_row(vi, sp.n1, sr)) * vstride;
-#pragma unroll
-        for (int pp = 0; pp < VPASS; ++pp)
-          if constexpr (FP8)
-            vv[pp][i] = vi == vnew ? newq[D / 8 + 16 * pp + l16]
-                                   : load_raw8<FP8, NT>(vbase, ev + 128 * pp + 8 * l16, vi < sp.v1);
-          else
-            vv[pp][i] = load_raw8<FP8, NT>(vi == vnew ? a.v_new : vbase,
-                                       (vi == vnew ? vnew_off : ev) + 128 * pp + 8 * l16, vi < sp.v1);
+        if constexpr (FP8)
+          vv[i] = vi == vnew ? *((const RawV*)(newq + D / 8) + l16)
+                             : load_raw<FP8, NT, VE>(vbase, ev + VE * l16, vi < sp.v1);
+        else
+          vv[i] = load_raw<FP8, NT, VE>(vi == vnew ? a.v_new : vbase, (vi == vnew ? vnew_off : ev) + VE * l16,
+                                        vi < sp.v1);
       }
     }
     RawT kn[KSTEPS], kn2[KSTEPS];
@@ -381,8 +397,8 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
     } else {
 #pragma unroll
       for (int t = 0; t < KSTEPS; ++t) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16x8_of<FP8>(ka[t])), qf[t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16x8_of<FP8>(kb[t])), qf[t], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(ka[t])), qf[t], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(kb[t])), qf[t], s1, 0, 0, 0);
       }
     }
     // raw dot products; the scale (> 0, fp8 key scale included) is applied to
@@ -410,9 +426,7 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
       const float mnew = up ? bm : m;
       const float alpha = up ? fast_exp2(m - mnew) : 1.f;
 #pragma unroll
-      for (int pp = 0; pp < VPASS; ++pp)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[pp][c] *= alpha;
+      for (int c = 0; c < VE; ++c) acc[c] *= alpha;
       lsum *= alpha;
       m = mnew;
       mref = m == -INFINITY ? 0.f : m;  // no valid row yet: every x is -inf, exp2 gives 0
@@ -421,24 +435,46 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) pe[i] = fast_exp2(fmaf(x[i], xs, -mref));
     lsum += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
-    u32x4 pw;
+    bf16x8 pb[PARTS];
+    if constexpr (PARTS == 1) {
+      u32x4 pw;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(pe[2 * i], pe[2 * i + 1]);
-    const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
+      for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(pe[2 * i], pe[2 * i + 1]);
+      pb[0] = __builtin_bit_cast(bf16x8, pw);
+    } else {
+      // 8 bits at a time, truncated, so no part is negative; the later parts
+      // are kept off zero (2^-126), so an infinite value times them stays
+      // infinite, as with the unsplit probability
 #pragma unroll
-    for (int pp = 0; pp < VPASS; ++pp) {
-      u32x4 vbf[8];
+      for (int part = 0; part < PARTS; ++part) {
+        u32x4 pw;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) vbf[i] = bf16x8_of<FP8>(vv[pp][i]);
+        for (int i = 0; i < 4; ++i) {
+          float hi[2];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const int u = c >> 1;
-        const uint32_t selb = (c & 1) ? 0x07060302u : 0x05040100u;
-        u32x4 av;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) av[i] = __builtin_amdgcn_perm(vbf[2 * i + 1][u], vbf[2 * i][u], selb);
-        acc[pp][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), pb, acc[pp][c], 0, 0, 0);
+          for (int k = 0; k < 2; ++k) {
+            float& r = pe[2 * i + k];
+            hi[k] = part ? fmaxf(r, 0x1p-126f) : r;
+            r -= __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+          }
+          pw[i] = __builtin_amdgcn_perm(__float_as_uint(hi[1]), __float_as_uint(hi[0]), 0x07060302u);
+        }
+        pb[part] = __builtin_bit_cast(bf16x8, pw);
       }
+    }
+    typename Raw<false, VE>::T vbf[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) vbf[i] = bf16_of<FP8, VE>(vv[i]);
+#pragma unroll
+    for (int c = 0; c < VE; ++c) {
+      const int u = c >> 1;
+      const uint32_t selb = (c & 1) ? 0x07060302u : 0x05040100u;
+      u32x4 av;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) av[i] = __builtin_amdgcn_perm(vbf[2 * i + 1][u], vbf[2 * i][u], selb);
+#pragma unroll
+      for (int part = PARTS - 1; part >= 0; --part)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), pb[part], acc[c], 0, 0, 0);
     }
 #pragma unroll
     for (int t = 0; t < KSTEPS; ++t) {
@@ -450,11 +486,11 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
   lsum += __shfl_xor(lsum, 32);
   if (has_newp) new_piece_store(a, g, slot, vnew, lane, newp);
   if constexpr (FP8) {
-    if (owns_new && lane < D / 8 + 16 * VPASS) {
+    if (owns_new && lane < 2 * (D / 8)) {
       const size_t crow = ((size_t)slot * a.Hkv + g) * (size_t)B + vnew;
       if (lane < D / 8)
         *((u32x2*)const_cast<void*>(a.ck) + crow * (D / 8) + lane) = newq[lane];
-      else
+      else if (PARTS == 1 || a.cv)
         *((u32x2*)const_cast<void*>(a.cv) + crow * (a.dv / 8) + (lane - D / 8)) = newq[lane];
     }
   }
@@ -463,16 +499,12 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
   if (lg == 0) a.ml[pi] = make_float2(m, lsum);
   float* dst = a.part + pi * a.dv;
 #pragma unroll
-  for (int pp = 0; pp < VPASS; ++pp)
+  for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float4 lo = make_float4(acc[pp][0][e], acc[pp][1][e], acc[pp][2][e], acc[pp][3][e]);
-      float4 hi = make_float4(acc[pp][4][e], acc[pp][5][e], acc[pp][6][e], acc[pp][7][e]);
-      lo.x *= vsc; lo.y *= vsc; lo.z *= vsc; lo.w *= vsc;
-      hi.x *= vsc; hi.y *= vsc; hi.z *= vsc; hi.w *= vsc;
-      float* d = dst + 128 * pp + 8 * (4 * lg + e);
-      *(float4*)d = lo;
-      *(float4*)(d + 4) = hi;
+    for (int c = 0; c < VE; c += 4) {
+      float4 o = make_float4(acc[c][e], acc[c + 1][e], acc[c + 2][e], acc[c + 3][e]);
+      o.x *= vsc; o.y *= vsc; o.z *= vsc; o.w *= vsc;
+      *(float4*)(dst + VE * (4 * lg + e) + c) = o;
     }
 }
 
@@ -490,7 +522,7 @@ __device__ __forceinline__ int mla_kcnt(int w) { return w < 2 ? 5 : 4; }
 template <bool FP8, bool NT>
 __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
   constexpr int D = kMlaKSteps * 32;  // 576
-  typedef typename Raw8<FP8>::T RawT;
+  typedef typename Raw<FP8>::T RawT;
   __shared__ f32x4 sbuf[2][4][2][64];  // [parity][wave][row set][lane]
   const int lane = tid() & 63, w = tid() >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
@@ -530,8 +562,8 @@ __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
     for (int t = 0; t < 5; ++t) {
       const int col = 32 * kb + 8 * (kc * lg + t);
       const bool tin = t < kc;
-      ka[t] = load_raw8<FP8, NT>(a.ck, ra * D + col, va < sp.v1 && tin);
-      kbv[t] = load_raw8<FP8, NT>(a.ck, rb * D + col, vb2 < sp.v1 && tin);
+      ka[t] = load_raw<FP8, NT>(a.ck, ra * D + col, va < sp.v1 && tin);
+      kbv[t] = load_raw<FP8, NT>(a.ck, rb * D + col, vb2 < sp.v1 && tin);
     }
   };
   RawT ka[5], kbv[5];
@@ -544,7 +576,7 @@ __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
     for (int i = 0; i < 8; ++i) {
       const int vi = vb + (i < 4 ? 4 * lg + i : 16 + 4 * lg + (i - 4));
       const size_t rr = row0 + virt_row(vi, sp.n1, sr);
-      vv[i] = load_raw8<FP8, NT>(a.ck, rr * D + 128 * w + 8 * l16, vi < sp.v1);
+      vv[i] = load_raw<FP8, NT>(a.ck, rr * D + 128 * w + 8 * l16, vi < sp.v1);
     }
     RawT kn[5], kn2[5];
     if (vb + 32 < sp.v1) load_k(vb + 32, kn, kn2);
@@ -553,8 +585,8 @@ __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
       if (t < kc) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16x8_of<FP8>(ka[t])), qf[t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16x8_of<FP8>(kbv[t])), qf[t], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(ka[t])), qf[t], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(kbv[t])), qf[t], s1, 0, 0, 0);
       }
     }
     sbuf[parity][w][0][lane] = s0;
@@ -602,7 +634,7 @@ __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
     const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
     u32x4 vbf[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) vbf[i] = bf16x8_of<FP8>(vv[i]);
+    for (int i = 0; i < 8; ++i) vbf[i] = bf16_of<FP8>(vv[i]);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const int u = c >> 1;
@@ -668,7 +700,7 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr_t;
 // One wave-instruction of global -> LDS copy (lane i's 16 bytes land at
 // lds_wave_base + 16*i), issued through inline asm so that the only ordering
 // with later LDS reads is the caller's explicit vmcnt wait and barrier.  M0
-// (the DMA's LDS base) is saved and restored around it.  NT as for load_raw8
+// (the DMA's LDS base) is saved and restored around it.  NT as for load_raw
 // (measured 3-7% faster on the 16 x 128k latent call).
 template <bool NT>
 __device__ __forceinline__ void dma16_lat(const void* g, const void* lds_wave_base) {
@@ -1261,7 +1293,11 @@ Geometry decode_geometry(const snap_params& p, int n) {
   // latent caches run 4-wave workgroups (two per CU), the others one wave each
   const bool latent = p.v_in_k && p.d_qk == 576;
   const bool latent_lds = latent && p.kv_dtype == SNAP_BF16;  // one 4-wave workgroup per CU (LDS-bound)
-  const int target = latent_lds ? kLatentLdsWGs : (latent ? 512 : 2048);
+  // 64-wide fp8 rows: 4 KB in flight per wave, so twice the waves (32 sequences
+  // x 16384 rows: 104.6 -> 93.5 us a call; 64-wide bf16 rows measured slower
+  // with them, 161.8 -> 183.5 us)
+  const bool narrow = p.d_qk == 64 && p.kv_dtype == SNAP_FP8_E4M3;
+  const int target = latent_lds ? kLatentLdsWGs : (latent ? 512 : (narrow ? 4096 : 2048));
   // rounded down: a grid just above the resident capacity would leave a
   // partial second round of workgroups (measured 25% slower on the fp8 GQA
   // kernel at 248 units: 9 chunks against 8)
@@ -1319,17 +1355,16 @@ snap_status launch_decode(const snap_params& p, const snap_cache& c, const int32
   a.k_new = nullptr;
   a.v_new = nullptr;
 
-  const bool mfma_ok = p.in_dtype == SNAP_BF16 && !p.v_in_k && p.d_qk == 128 && p.d_v == 128 &&
-                       (p.kv_dtype == SNAP_BF16 || p.kv_dtype == SNAP_FP8_E4M3);
+  const bool mfma_ok = p.in_dtype == SNAP_BF16 && p.d_qk == p.d_v;  // 64 or 128 wide rows, bf16 or fp8
   const bool mla_ok = p.in_dtype == SNAP_BF16 && p.v_in_k && p.n_kv_heads == 1 && p.d_qk == 576 && p.d_v == 512 &&
                       (p.kv_dtype == SNAP_BF16 || p.kv_dtype == SNAP_FP8_E4M3);
   if (k_new) {
-    // the MFMA kernels (GQA: bf16 and fp8 caches; latent: bf16) take the new
-    // token in the same launch; the others run the append kernel first (same
+    // the MFMA kernels (64- and 128-wide rows: bf16 and fp8 caches; latent:
+    // bf16) take the new token in the same launch; the others run the append kernel first (same
     // result)
     if (mfma_ok || (mla_ok && p.kv_dtype == SNAP_BF16)) {
       a.k_new = k_new;
-      a.v_new = p.v_in_k ? nullptr : v_new;
+      a.v_new = p.v_in_k ? k_new : v_new;  // without a V cache the new value row is the key row
     } else {
       const snap_status st = launch_append(p, c, pos, n, slot_ids, k_new, v_new, stream);
       if (st != SNAP_OK) return st;
@@ -1353,21 +1388,23 @@ snap_status launch_decode(const snap_params& p, const snap_cache& c, const int32
   } else if (mfma_ok) {
     dim3 grid(geo.n_chunks, n * p.n_kv_heads);
     void (*k)(DecodeArgs);
-    if (p.kv_dtype == SNAP_FP8_E4M3 && p.fp8_qk)
+    const bool fp8 = p.kv_dtype == SNAP_FP8_E4M3;
+    if (p.d_qk == 64)  // 32-bit probabilities (three bf16 parts)
+      k = fp8 ? (nt ? decode_mfma<2, 3, true, false, true> : decode_mfma<2, 3, true, false, false>)
+              : (nt ? decode_mfma<2, 3, false, false, true> : decode_mfma<2, 3, false, false, false>);
+    else if (p.v_in_k)
+      k = fp8 ? (nt ? decode_mfma<4, 3, true, false, true> : decode_mfma<4, 3, true, false, false>)
+              : (nt ? decode_mfma<4, 3, false, false, true> : decode_mfma<4, 3, false, false, false>);
+    else if (fp8 && p.fp8_qk)
       k = nt ? decode_mfma<4, 1, true, true, true> : decode_mfma<4, 1, true, true, false>;
-    else if (p.kv_dtype == SNAP_FP8_E4M3)
+    else if (fp8)
       k = nt ? decode_mfma<4, 1, true, false, true> : decode_mfma<4, 1, true, false, false>;
     else
       k = nt ? decode_mfma<4, 1, false, false, true> : decode_mfma<4, 1, false, false, false>;
     hipLaunchKernelGGL(k, grid, dim3(64), 0, stream, a);
   } else {
     dim3 grid(geo.n_chunks, n * p.n_q_heads);
-    if (p.kv_dtype == SNAP_F32)
-      hipLaunchKernelGGL((decode_generic<float>), grid, dim3(64), 0, stream, a);
-    else if (p.kv_dtype == SNAP_BF16)
-      hipLaunchKernelGGL((decode_generic<uint16_t>), grid, dim3(64), 0, stream, a);
-    else
-      hipLaunchKernelGGL((decode_generic<uint8_t>), grid, dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((decode_generic<float>), grid, dim3(64), 0, stream, a);
   }
   if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
   CombineArgs ca;

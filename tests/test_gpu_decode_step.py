@@ -174,3 +174,50 @@ def test_load_hint_keeps_results(kind):
         assert diff <= 1e-4 * max(1.0, float(a.abs().max()))
     else:
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+# 64-wide rows and caches whose values are the key rows keep 32-bit
+# probabilities (split into three bf16 parts for the value product), so with
+# fp32 outputs they are held to the fp32 bound.
+@pytest.mark.parametrize("d,v_in_k,kv,hq,hkv,stream", [
+    (64, False, "bf16", 8, 2, False),
+    (64, False, "bf16", 16, 1, True),   # 16 heads fill the matrix instruction's columns
+    (64, False, "fp8", 6, 2, True),
+    (64, False, "fp8", 2, 2, False),
+    (64, True, "bf16", 3, 1, False),
+    (64, True, "fp8", 8, 2, True),
+    (128, True, "bf16", 8, 2, True),
+    (128, True, "fp8", 4, 4, False),
+])
+def test_step_with_32_bit_probabilities(d, v_in_k, kv, hq, hkv, stream):
+    wl = synth.small(GQA, name="step-32bit", n_q_heads=hq, n_kv_heads=hkv, d_qk=d, d_v=d, v_in_k=v_in_k, kv_dtype=kv,
+                     topk=301, obs_window=8, rope=not v_in_k, plant_frac=None if v_in_k else 0.01)
+    p = params_of(wl, kv_reuse=snap.SNAP_KV_STREAM if stream else snap.SNAP_KV_KEEP)
+    lengths = [2900, 2, 333]
+    _announce(f"decode_step d {d} v_in_k {int(v_in_k)} cache {kv} heads {hq}/{hkv} stream {int(stream)}: {lengths}")
+    b = _fused_vs_two_calls(wl, p, lengths, [2, 0, 1], 4, 24, torch.bfloat16, invalid_slot=True)
+    err = decode_steps(p, wl, b, [2, 0, 1], 4, torch.float32, TOL["f32"], salt=7, fused="alt")
+    print(f"  max abs err vs oracle: {err:.3e}", flush=True)
+
+
+@pytest.mark.parametrize("kv_reuse", [snap.SNAP_KV_KEEP, snap.SNAP_KV_STREAM])
+def test_infinite_value_stays_infinite(kv_reuse):
+    """A value row holding +inf and -inf (bf16 overflow) makes those output
+    dims infinite of that sign, whatever the later parts of its split
+    probability are, and leaves the others finite."""
+    wl = synth.small(GQA, name="step-inf", d_qk=64, d_v=64, plant_frac=None)
+    p = params_of(wl, kv_reuse=kv_reuse)
+    _announce(f"infinite values, d 64, kv_reuse {kv_reuse}")
+    q, k, v = synth.prefill_batch(wl, 0, [700])
+    c = GpuCache(p, 1)
+    gpu_compress(p, c, q, k, v, [700], [0], debug=False)
+    c.v[0, :, 7, 5] = float("inf")
+    c.v[0, :, 40, 9] = float("-inf")
+    sl = torch.tensor([0], dtype=torch.int32, device="cuda")
+    qd, kn, vn = synth.decode_inputs(wl, 0, 0, [700], device="cuda")
+    qd[0, 0] = 0  # equal logits: every probability is 1, its later parts are zero
+    out = torch.zeros((1, p.n_q_heads, p.d_v), dtype=torch.float32, device="cuda")
+    snap.snap_decode_step(p, c.c(), c.pos, c.n_topk, sl, qd, kn, vn, out, snap.workspace(snap.snap_decode_workspace(p, 1)))
+    torch.cuda.synchronize()
+    assert (out[0, :, 5] == float("inf")).all() and (out[0, :, 9] == float("-inf")).all()
+    assert torch.isfinite(out[0, :, [d for d in range(64) if d not in (5, 9)]]).all()
