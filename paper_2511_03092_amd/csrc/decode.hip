@@ -12,12 +12,12 @@
 //   decode_mla_lds bf16 latent rows (576 wide, values = first 512 dims): four
 //                  waves per (chunk, sequence) streaming 32-row blocks through
 //                  a 4-stage LDS ring
-//   decode_mla     fp8 latent rows, register-streamed
+//   decode_mla8_lds  the same for fp8 latent rows, in 64-row blocks
 //   decode_generic one wave per (chunk, sequence, query head): fp32 caches and
 //                  latent caches of several KV heads
 //   combine        log-sum-exp merge of the chunk partials -> out
-// decode_mfma (bf16 and fp8 caches) and decode_mla_lds (bf16) also take the
-// new token (snap_decode_step): the append happens in the same launch.
+// All but decode_generic also take the new token (snap_decode_step): the append
+// happens in the same launch.
 #include <math.h>
 
 #include "snap_internal.h"
@@ -508,167 +508,6 @@ __global__ __launch_bounds__(64) void decode_mfma(DecodeArgs a) {
     }
 }
 
-// ---------------------------------------------------------------- latent (MLA) decode
-// One workgroup of 4 waves per (chunk, sequence) of a shared 576-wide latent
-// cache (values = first 512 dims).  Per block of 32 rows, wave w computes the
-// partial logits over its share of the 18 k-steps of 32 dims (5,5,4,4), the
-// four partials are summed through LDS in a fixed order (so every wave holds
-// identical logits), and wave w then runs the value product for dims
-// [128w, 128w+128).  Heads beyond G (<= 16) are zero columns.
-constexpr int kMlaKSteps = 18;
-__device__ __forceinline__ int mla_kbeg(int w) { return w < 2 ? 5 * w : 10 + 4 * (w - 2); }
-__device__ __forceinline__ int mla_kcnt(int w) { return w < 2 ? 5 : 4; }
-
-template <bool FP8, bool NT>
-__global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
-  constexpr int D = kMlaKSteps * 32;  // 576
-  typedef typename Raw<FP8>::T RawT;
-  __shared__ f32x4 sbuf[2][4][2][64];  // [parity][wave][row set][lane]
-  const int lane = tid() & 63, w = tid() >> 6;
-  const int l16 = lane & 15, lg = lane >> 4;
-  const int chunk = bid_x(), b = bid_y();  // one KV head
-  int slot;
-  RowSpan sp;
-  if (!span_of(a, b, chunk, slot, sp)) return;
-  const int sr = a.sink + a.recent;
-  const int B = sr + a.topk;
-  const int h = l16;
-  const bool hval = h < a.G;
-  const int kb = mla_kbeg(w), kc = mla_kcnt(w);
-
-  bf16x8 qf[5];
-  {
-    const uint16_t* qp = (const uint16_t*)a.q + ((size_t)b * a.Hq + (hval ? h : 0)) * D;
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (hval && t < kc) v = *(const u32x4*)(qp + 32 * kb + 8 * (kc * lg + t));
-      qf[t] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  const size_t row0 = (size_t)slot * B;
-  const float ksc = FP8 ? a.k_scale[slot] : 1.f;
-  const float xs = a.scale * kLog2e * ksc;
-
-  float m = -INFINITY, mref = 0.f, lsum = 0.f;  // reference max (log2 units), its finite stand-in, sum
-  f32x4 acc[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto load_k = [&](int vb, RawT* ka, RawT* kbv) {
-    const int va = vb + l16, vb2 = vb + 16 + l16;
-    const size_t ra = row0 + virt_row(va, sp.n1, sr), rb = row0 + virt_row(vb2, sp.n1, sr);
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      const int col = 32 * kb + 8 * (kc * lg + t);
-      const bool tin = t < kc;
-      ka[t] = load_raw<FP8, NT>(a.ck, ra * D + col, va < sp.v1 && tin);
-      kbv[t] = load_raw<FP8, NT>(a.ck, rb * D + col, vb2 < sp.v1 && tin);
-    }
-  };
-  RawT ka[5], kbv[5];
-  if (sp.v0 < sp.v1) load_k(sp.v0, ka, kbv);
-
-  int parity = 0;
-  for (int vb = sp.v0; vb < sp.v1; vb += 32, parity ^= 1) {
-    RawT vv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int vi = vb + (i < 4 ? 4 * lg + i : 16 + 4 * lg + (i - 4));
-      const size_t rr = row0 + virt_row(vi, sp.n1, sr);
-      vv[i] = load_raw<FP8, NT>(a.ck, rr * D + 128 * w + 8 * l16, vi < sp.v1);
-    }
-    RawT kn[5], kn2[5];
-    if (vb + 32 < sp.v1) load_k(vb + 32, kn, kn2);
-
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      if (t < kc) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(ka[t])), qf[t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf16_of<FP8>(kbv[t])), qf[t], s1, 0, 0, 0);
-      }
-    }
-    sbuf[parity][w][0][lane] = s0;
-    sbuf[parity][w][1][lane] = s1;
-    __syncthreads();
-    s0 = ((sbuf[parity][0][0][lane] + sbuf[parity][1][0][lane]) + sbuf[parity][2][0][lane]) + sbuf[parity][3][0][lane];
-    s1 = ((sbuf[parity][0][1][lane] + sbuf[parity][1][1][lane]) + sbuf[parity][2][1][lane]) + sbuf[parity][3][1][lane];
-    // raw dot products; the scale (> 0, fp8 key scale included) is applied to
-    // the block max and folded into the exponent
-    float x[8];
-    if (vb + 32 <= sp.v1) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[e] = s0[e];
-        x[4 + e] = s1[e];
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[e] = (vb + 4 * lg + e < sp.v1) ? s0[e] : -INFINITY;
-        x[4 + e] = (vb + 16 + 4 * lg + e < sp.v1) ? s1[e] : -INFINITY;
-      }
-    }
-    float bm = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-    bm = fmaxf(bm, __shfl_xor(bm, 16));
-    bm = fmaxf(bm, __shfl_xor(bm, 32));
-    bm *= xs;
-    const bool up = bm > m + kStaleMax;  // always true for the first valid block (m = -inf)
-    if (wave_any(up)) {
-      const float mnew = up ? bm : m;
-      const float alpha = up ? fast_exp2(m - mnew) : 1.f;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] *= alpha;
-      lsum *= alpha;
-      m = mnew;
-      mref = m == -INFINITY ? 0.f : m;  // no valid row yet: every x is -inf, exp2 gives 0
-    }
-    float pe[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) pe[i] = fast_exp2(fmaf(x[i], xs, -mref));
-    lsum += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
-    u32x4 pw;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(pe[2 * i], pe[2 * i + 1]);
-    const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
-    u32x4 vbf[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) vbf[i] = bf16_of<FP8>(vv[i]);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int u = c >> 1;
-      const uint32_t selb = (c & 1) ? 0x07060302u : 0x05040100u;
-      u32x4 av;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = __builtin_amdgcn_perm(vbf[2 * i + 1][u], vbf[2 * i][u], selb);
-      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), pb, acc[c], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      ka[t] = kn[t];
-      kbv[t] = kn2[t];
-    }
-  }
-  lsum += __shfl_xor(lsum, 16);
-  lsum += __shfl_xor(lsum, 32);
-  if (!hval) return;
-  const size_t pi = ((size_t)b * a.Hq + h) * a.n_chunks + chunk;
-  if (w == 0 && lg == 0) a.ml[pi] = make_float2(m, lsum);
-  const float vsc = FP8 ? a.k_scale[slot] : 1.f;
-  float* dst = a.part + pi * a.dv + 128 * w;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float4 lo = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
-    float4 hi = make_float4(acc[4][e], acc[5][e], acc[6][e], acc[7][e]);
-    lo.x *= vsc; lo.y *= vsc; lo.z *= vsc; lo.w *= vsc;
-    hi.x *= vsc; hi.y *= vsc; hi.z *= vsc; hi.w *= vsc;
-    float* d = dst + 8 * (4 * lg + e);
-    *(float4*)d = lo;
-    *(float4*)(d + 4) = hi;
-  }
-}
-
 // ---------------------------------------------------------------- latent decode, LDS-staged
 // bf16 latent caches (576-wide rows, values = first 512 dims).  One workgroup
 // of 4 waves per (chunk, sequence) streams blocks of 32 rows through a ring
@@ -687,6 +526,7 @@ __global__ __launch_bounds__(256) void decode_mla(DecodeArgs a) {
 // Four 36 KB stages (147 KB of the 160 KB LDS: one workgroup per CU); a
 // stage is refilled once every wave has consumed it, so four blocks are in
 // flight when block i is waited for.
+constexpr int kMlaKSteps = 18;
 constexpr int kLatStages = 4;
 constexpr int kLatRowBytes = 576 * 2;
 constexpr int kLatChunks = kLatRowBytes / 16;        // 72
@@ -941,6 +781,229 @@ __global__ __launch_bounds__(256) void decode_mla_lds(DecodeArgs a) {
   for (int e = 0; e < 4; ++e) {
     float4 lo = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
     float4 hi = make_float4(acc[4][e], acc[5][e], acc[6][e], acc[7][e]);
+    float* d = dst + 8 * (4 * lg + e);
+    *(float4*)d = lo;
+    *(float4*)(d + 4) = hi;
+  }
+}
+
+// ---------------------------------------------------------------- fp8 latent decode, LDS-staged
+// fp8 latent caches: one workgroup of 4 waves per (chunk, sequence) streams
+// blocks of 64 rows (576 codes each: as many bytes per stage as 32 bf16 rows)
+// through LDS with direct loads.  Converting codes to bf16 is what a CU would
+// run out of first, so no wave converts a code that another wave converts for
+// the same product: wave w forms the logits of the block's rows [16w, 16w+16)
+// over all 18 k-steps, the 64 x 16 logits are exchanged through LDS, and every
+// wave then takes the softmax of all 64 rows (the same values in each) and the
+// value product for dims [128w, 128w+128).  Two stages (74 KB), so that two
+// workgroups share a CU and one computes while the other waits: 16 heads, 32
+// sequences x 32768 rows 120 us with four stages and one workgroup, 107 us with
+// two.  HBM bound there (5.7 TB/s; 366 us with the rows loaded to registers, an
+// exchange and barrier per 32 rows and an append launch before it); 8 heads, 8
+// x 16384 rows 34.0 -> 22.4 us a call.
+// LDS rows are 36 chunks of 16 bytes; chunk c of row r sits at slot
+// r*36 + (c ^ ((r >> 1) & 3)), which spreads one chunk of 8 consecutive rows
+// (a key-fragment read) over the banks and keeps a value read within its 128
+// bytes.
+constexpr int kLat8Stages = 2;
+constexpr int kLat8Rows = 64;
+constexpr int kLat8RowBytes = 576;
+constexpr int kLat8Chunks = kLat8RowBytes / 16;  // 36
+static_assert(kLat8Rows * kLat8RowBytes == kLatBlockBytes, "the stages hold either block");
+constexpr int kLat8Ld = kLat8Rows + 4;  // logits of one head (padded: 16 heads read 16 bytes each)
+
+__device__ __forceinline__ int lat8_slot(int r, int c) { return r * kLat8Chunks + (c ^ ((r >> 1) & 3)); }
+
+template <bool NT>
+__global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
+  __shared__ __align__(16) unsigned char stage[kLat8Stages][kLatBlockBytes];
+  __shared__ __align__(16) float logits[16][kLat8Ld];
+  const int lane = tid() & 63, w = tid() >> 6;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int chunk = bid_x(), b = bid_y();
+  int slot;
+  RowSpan sp;
+  if (!span_of(a, b, chunk, slot, sp)) return;
+  const int sr = a.sink + a.recent;
+  const int B = sr + a.topk;
+  const bool hval = l16 < a.G;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const float ksc = a.k_scale[slot];
+
+  // this lane's share of every block load: (row, chunk) of its 9 slots
+  int ld_r[kLatLoadsPerWave], ld_c[kLatLoadsPerWave], ld_off[kLatLoadsPerWave];
+#pragma unroll
+  for (int ii = 0; ii < kLatLoadsPerWave; ++ii) {
+    const int q = (wu + 4 * ii) * 64 + lane;
+    const int r = q / kLat8Chunks;
+    ld_r[ii] = r;
+    ld_c[ii] = (q % kLat8Chunks) ^ ((r >> 1) & 3);
+    ld_off[ii] = r * kLat8RowBytes + ld_c[ii] * 16;
+  }
+  const unsigned char* cache = (const unsigned char*)a.ck + (size_t)slot * B * kLat8RowBytes;
+  // the slot's 64-row blocks are interleaved over its chunks, as in decode_mla_lds
+  const int nb_slot = (sp.nv + kLat8Rows - 1) / kLat8Rows;
+  const int nblk =
+      __builtin_amdgcn_readfirstlane(chunk < nb_slot ? (nb_slot - chunk + a.n_chunks - 1) / a.n_chunks : 0);
+  // fused append: the workgroup whose block holds row vnew quantises it
+  // (thread t: codes 8t .. 8t+7), puts the codes over that row of the block in
+  // LDS and stores them into the cache at its end; no other workgroup reads
+  // the row
+  const int vnew = new_row(a, slot);
+  const int blk_new = vnew >= 0 && vnew < sp.nv && vnew / kLat8Rows % a.n_chunks == chunk
+                          ? vnew / kLat8Rows / a.n_chunks : -1;
+  const bool has_new = blk_new >= 0 && tid() < kLat8RowBytes / 8;
+  u32x2 codes = {0u, 0u};
+  if (has_new) codes = new_raw8<true>(a.k_new, (size_t)b * kLat8RowBytes + 8 * tid(), ksc);
+
+  auto issue = [&](int blk) {
+    const int vb = kLat8Rows * (chunk + blk * a.n_chunks);
+    unsigned char* dst = &stage[blk % kLat8Stages][0];
+    if (vb + kLat8Rows <= sp.nv && (vb + kLat8Rows <= sp.n1 || vb >= sp.n1)) {
+      // a whole block inside one run of the row map
+      const unsigned char* base = cache + (size_t)virt_row(vb, sp.n1, sr) * kLat8RowBytes;
+#pragma unroll
+      for (int ii = 0; ii < kLatLoadsPerWave; ++ii) dma16_lat<NT>(base + ld_off[ii], dst + (size_t)(wu + 4 * ii) * 1024);
+    } else {
+#pragma unroll
+      for (int ii = 0; ii < kLatLoadsPerWave; ++ii) {
+        int v = vb + ld_r[ii];
+        v = v < sp.nv ? v : sp.nv - 1;
+        dma16_lat<NT>(cache + (size_t)virt_row(v, sp.n1, sr) * kLat8RowBytes + ld_c[ii] * 16,
+                      dst + (size_t)(wu + 4 * ii) * 1024);
+      }
+    }
+  };
+
+  const float xs = a.scale * kLog2e * ksc;
+  float m = -INFINITY, mref = 0.f, lsum = 0.f;  // reference max (log2 units), its finite stand-in, sum
+  f32x4 acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 qf[kMlaKSteps];  // lane group lg holds dims 8*(18*lg + t) of k-step t
+
+  // Prologue: the query rows (G x 1152 bytes) go to the second stage with block
+  // 0, so one wait covers both.
+  if (nblk > 0) {
+    const int qchunks = a.G * kLatChunks;
+    const int nq = (qchunks + 63) / 64;  // wave-instructions (G <= 16: at most 18)
+    const unsigned char* qsrc = (const unsigned char*)a.q + (size_t)b * a.Hq * kLatRowBytes;
+    unsigned char* qdst = &stage[kLat8Stages - 1][0];
+    for (int ii = wu; ii < nq; ii += 4) {
+      int qc = ii * 64 + lane;
+      qc = qc < qchunks ? qc : 0;  // the last instruction's spare lanes re-read chunk 0
+      dma16_lat<NT>(qsrc + (size_t)qc * 16, qdst + (size_t)ii * 1024);
+    }
+    issue(0);
+    lat_wait_vm<0>();
+    lat_barrier();
+#pragma unroll
+    for (int t = 0; t < kMlaKSteps; ++t) {
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (hval) v = *(const u32x4*)(qdst + (size_t)l16 * kLatRowBytes + 8 * (kMlaKSteps * lg + t) * 2);
+      qf[t] = __builtin_bit_cast(bf16x8, v);
+    }
+  }
+
+  for (int i = 0; i < nblk; ++i) {
+    // block i is in LDS for every wave, and every wave is done with block i-1
+    // (block 0: with the query rows), whose stage takes block i+1
+    lat_wait_vm<0>();
+    lat_barrier();
+    if (i + 1 < nblk) issue(i + 1);
+    unsigned char* st = &stage[i % kLat8Stages][0];
+    const int vb = kLat8Rows * (chunk + i * a.n_chunks);
+    if (i == blk_new) {
+      if (has_new) {
+        const int r = vnew - vb;
+        *(u32x2*)(st + lat8_slot(r, tid() >> 1) * 16 + 8 * (tid() & 1)) = codes;
+      }
+      lat_barrier();
+    }
+
+    // logits of rows 16w .. 16w+15 (two chains, summed)
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < kMlaKSteps / 2; ++j) {
+      const u32x4 kk = *(const u32x4*)(st + (size_t)lat8_slot(16 * w + l16, 9 * lg + j) * 16);
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, e4m3x8_to_bf16x8(u32x2{kk[0], kk[1]})),
+                                                   qf[2 * j], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, e4m3x8_to_bf16x8(u32x2{kk[2], kk[3]})),
+                                                   qf[2 * j + 1], s1, 0, 0, 0);
+    }
+    s0 += s1;
+    *(f32x4*)&logits[l16][16 * w + 4 * lg] = s0;
+    lat_barrier();
+
+    // softmax of the block's 64 rows for head l16: this lane takes rows
+    // 16k + 4*lg + e
+    f32x4 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = *(const f32x4*)&logits[l16][16 * k + 4 * lg];
+    if (vb + kLat8Rows > sp.nv) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (vb + 16 * k + 4 * lg + e >= sp.nv) x[k][e] = -INFINITY;
+    }
+    float bm = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bm = fmaxf(bm, fmaxf(fmaxf(x[k][0], x[k][1]), fmaxf(x[k][2], x[k][3])));
+    bm = fmaxf(bm, __shfl_xor(bm, 16));
+    bm = fmaxf(bm, __shfl_xor(bm, 32));
+    bm *= xs;
+    const bool up = bm > m + kStaleMax;  // always true for the first valid block (m = -inf)
+    if (wave_any(up)) {
+      const float mnew = up ? bm : m;
+      const float alpha = up ? fast_exp2(m - mnew) : 1.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+      lsum *= alpha;
+      m = mnew;
+      mref = m == -INFINITY ? 0.f : m;  // no valid row yet: every x is -inf, exp2 gives 0
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {  // rows 32h .. 32h+31
+      float pe[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) pe[k] = fast_exp2(fmaf(x[2 * h + (k >> 2)][k & 3], xs, -mref));
+      lsum += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
+      u32x4 pw;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pw[k] = pack_bf16x2(pe[2 * k], pe[2 * k + 1]);
+      const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
+      u32x4 vv[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int r = 32 * h + (k < 4 ? 4 * lg + k : 16 + 4 * lg + (k - 4));
+        vv[k] = e4m3x8_to_bf16x8(*(const u32x2*)(st + (size_t)lat8_slot(r, 8 * w + (l16 >> 1)) * 16 + 8 * (l16 & 1)));
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int u = c >> 1;
+        const uint32_t selb = (c & 1) ? 0x07060302u : 0x05040100u;
+        u32x4 av;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) av[k] = __builtin_amdgcn_perm(vv[2 * k + 1][u], vv[2 * k][u], selb);
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), pb, acc[c], 0, 0, 0);
+      }
+    }
+  }
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
+  if (has_new)
+    *((u32x2*)const_cast<void*>(a.ck) + ((size_t)slot * B + vnew) * (kLat8RowBytes / 8) + tid()) = codes;
+  if (!hval) return;
+  const size_t pi = ((size_t)b * a.Hq + l16) * a.n_chunks + chunk;
+  if (w == 0 && lg == 0) a.ml[pi] = make_float2(m, lsum);
+  float* dst = a.part + pi * a.dv + 128 * w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float4 lo = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
+    float4 hi = make_float4(acc[4][e], acc[5][e], acc[6][e], acc[7][e]);
+    lo.x *= ksc; lo.y *= ksc; lo.z *= ksc; lo.w *= ksc;
+    hi.x *= ksc; hi.y *= ksc; hi.z *= ksc; hi.w *= ksc;
     float* d = dst + 8 * (4 * lg + e);
     *(float4*)d = lo;
     *(float4*)(d + 4) = hi;
@@ -1290,9 +1353,9 @@ Geometry decode_geometry(const snap_params& p, int n) {
   Geometry g{};
   const int B = p.sink + p.recent + p.topk;
   const int units = (n > 0 ? n : 1) * p.n_kv_heads;
-  // latent caches run 4-wave workgroups (two per CU), the others one wave each
+  // latent caches run 4-wave workgroups, the others one wave each
   const bool latent = p.v_in_k && p.d_qk == 576;
-  const bool latent_lds = latent && p.kv_dtype == SNAP_BF16;  // one 4-wave workgroup per CU (LDS-bound)
+  const bool latent_lds = latent && p.kv_dtype == SNAP_BF16;  // one per CU (LDS-bound), else two
   // 64-wide fp8 rows: 4 KB in flight per wave, so twice the waves (32 sequences
   // x 16384 rows: 104.6 -> 93.5 us a call; 64-wide bf16 rows measured slower
   // with them, 161.8 -> 183.5 us)
@@ -1359,10 +1422,9 @@ snap_status launch_decode(const snap_params& p, const snap_cache& c, const int32
   const bool mla_ok = p.in_dtype == SNAP_BF16 && p.v_in_k && p.n_kv_heads == 1 && p.d_qk == 576 && p.d_v == 512 &&
                       (p.kv_dtype == SNAP_BF16 || p.kv_dtype == SNAP_FP8_E4M3);
   if (k_new) {
-    // the MFMA kernels (64- and 128-wide rows: bf16 and fp8 caches; latent:
-    // bf16) take the new token in the same launch; the others run the append kernel first (same
-    // result)
-    if (mfma_ok || (mla_ok && p.kv_dtype == SNAP_BF16)) {
+    // the MFMA kernels take the new token in the same launch; the generic one
+    // runs the append kernel first (same result)
+    if (mfma_ok || mla_ok) {
       a.k_new = k_new;
       a.v_new = p.v_in_k ? k_new : v_new;  // without a V cache the new value row is the key row
     } else {
@@ -1381,7 +1443,7 @@ snap_status launch_decode(const snap_params& p, const snap_cache& c, const int32
     dim3 grid(geo.n_chunks, n);
     void (*k)(DecodeArgs);
     if (p.kv_dtype == SNAP_FP8_E4M3)
-      k = nt ? decode_mla<true, true> : decode_mla<true, false>;
+      k = nt ? decode_mla8_lds<true> : decode_mla8_lds<false>;
     else
       k = nt ? decode_mla_lds<true> : decode_mla_lds<false>;
     hipLaunchKernelGGL(k, grid, dim3(256), 0, stream, a);

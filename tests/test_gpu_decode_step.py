@@ -93,6 +93,22 @@ def test_step_latent_bf16_fused_kernel():
     print(f"  fused decode max abs err vs oracle: {err:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("hq,recent,topk,lengths", [
+    (8, 64, 1000, [3000, 3, 1500]),    # the ring wraps over a block boundary; a prompt shorter than the sinks
+    (16, 60, 64, [200, 1, 127]),       # one or two 64-row blocks, most workgroups with none
+    (3, 192, 700, [70, 900, 255]),     # the new row in the ragged last block
+])
+def test_step_latent_fp8_fused_kernel(hq, recent, topk, lengths):
+    wl = synth.small(synth.WORKLOADS["mla-8head-61layer-b16-128k"], n_q_heads=hq, recent=recent, topk=topk,
+                     obs_window=8, kv_dtype="fp8")
+    for hint in (snap.SNAP_KV_KEEP, snap.SNAP_KV_STREAM):
+        p = params_of(wl, kv_reuse=hint)
+        _announce(f"decode_step fp8 latent (fused LDS kernel), {hq} heads, hint {hint}: lengths {lengths}, ring {recent}")
+        b = _fused_vs_two_calls(wl, p, lengths, [0, 1, 2], 3, 70, torch.bfloat16, invalid_slot=True)
+        err = decode_steps(p, wl, b, [0, 1, 2], 4, torch.float32, TOL["fp8"], salt=7, fused="alt")
+        print(f"  max abs err vs oracle: {err:.3e}", flush=True)
+
+
 def test_step_fp8_fused_and_fp32_two_launch_paths():
     wl = synth.small(GQA, kv_dtype="fp8")
     p = params_of(wl)

@@ -16,10 +16,10 @@ Which kernels each case reaches (csrc names):
   G = 1, G = 3               score rows that leave waves empty or ragged
   latent 576, w = 16         the four-wave 576-wide score passes
   latent fp8                 fp8 latent assembly (given and data scales),
-                             decode_mla<fp8>
+                             decode_mla8_lds
   *-stream                   kv_reuse = SNAP_KV_STREAM: the streaming-load
                              instantiations of decode_mfma (bf16, fp8),
-                             decode_mla_lds and decode_mla<fp8>, which the
+                             decode_mla_lds and decode_mla8_lds, which the
                              default hint picks only for calls of 128 MiB and
                              more (the full-size tests)
 
