@@ -7,6 +7,22 @@
 
 namespace snap {
 
+// LDS tile of keys stored row by row, CPR 16-byte chunks per key: chunk c of
+// key k sits at slot k*CPR + (c ^ tile_swz<CPR>(k)).  The loads of a tile then
+// read contiguous memory (64 lanes cover whole rows; chunk by chunk, each load
+// instruction touched 64 cache lines), and a fragment read -- lane (l16, lg)
+// reads chunk 4t + lg of key l16 -- has distinct slots mod 16 over every 16
+// lanes that a 16-byte LDS read serves together (lanes 0-3, 12-15, 20-27 and
+// their like), so it is free of bank conflicts.  The chunk order 4t + lg is
+// part of that: with KSTEPS*lg + t, lanes of two groups meet in the same banks.
+template <int CPR>
+__device__ __forceinline__ int tile_swz(int key) {
+  static_assert(CPR % 8 == 0, "rows of whole 128-byte pieces");
+  return CPR % 16 == 0 ? key & 15 : (key >> 1) & 7;
+}
+template <int CPR>
+__device__ __forceinline__ int row_slot(int key, int c) { return key * CPR + (c ^ tile_swz<CPR>(key)); }
+
 // LDS tile of TK keys (64, or 32 for 576-wide rows) stored chunk-major: the
 // 16-byte chunk c of key k sits at slot c*TK + k.  A fragment read by 16
 // consecutive keys of one chunk is 256 contiguous bytes, and every tile load
@@ -41,6 +57,73 @@ __device__ __forceinline__ void dma16(const void* g, const void* lds_wave_base) 
       : "memory");
 }
 
+// The same with the address as a uniform base and a 32-bit lane offset.  Five
+// wait states stand between whatever wrote the base (a vector instruction may
+// have) and the load that reads it.
+__device__ __forceinline__ void dma16(const unsigned char* base, uint32_t off, const void* lds_wave_base) {
+  const uint32_t la = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)lds_wave_base);
+  const uint64_t ba = (uint64_t)(uintptr_t)base;
+  // readfirstlane returns int: through uint32_t, so that no sign reaches the high half
+  const uint32_t blo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ba);
+  const uint32_t bhi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(ba >> 32));
+  const uint64_t sb = (uint64_t)blo | (uint64_t)bhi << 32;
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 2\n\t"
+      "global_load_lds_dwordx4 %2, %3\n\t"
+      "s_nop 0\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(la), "v"(off), "s"(sb)
+      : "memory");
+}
+
+// One wave's share of every key tile: the tile is CPR*TK/64 wave-instructions,
+// each moving 64 x 16 bytes straight into LDS (no VGPRs); wave w issues
+// instructions w, w+NW, ...  This lane's key and byte offset within the tile,
+// once per kernel.
+template <int CPR, int NW, int TK>
+struct TileLoad {
+  static constexpr int NI = CPR * TK / 64;
+  static constexpr int KMAX = (NI + NW - 1) / NW;  // loads of the busiest wave
+  static_assert(CPR * TK % 64 == 0, "a tile is a whole number of wave-instructions");
+  int w;
+  int key[KMAX];
+  uint32_t off[KMAX];
+  __device__ __forceinline__ void init(int wave, int lane) {
+    w = __builtin_amdgcn_readfirstlane(wave);
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+      const unsigned slot = (unsigned)(w + k * NW) * 64u + (unsigned)lane;
+      const int kk = (int)(slot / CPR), c = (int)(slot % CPR) ^ tile_swz<CPR>(kk);
+      key[k] = kk;
+      off[k] = (uint32_t)(kk * CPR + c) * 16u;
+    }
+  }
+  // The tile of keys [t0, t0+TK) of the rows at kbase into buf.  Keys past c1
+  // read key c1-1 instead (c1 > t0), so a wave always issues the same number
+  // of loads per tile (those bytes are never used).
+  __device__ __forceinline__ void issue(const unsigned char* kbase, int t0, int c1, unsigned char* buf) const {
+    const unsigned char* base = kbase + (size_t)t0 * (CPR * 16);
+    const int last = c1 - 1 - t0;
+    if (last >= TK - 1) {
+#pragma unroll
+      for (int k = 0; k < KMAX; ++k) {
+        if (NI % NW != 0 && w + k * NW >= NI) break;  // wave-uniform
+        dma16(base, off[k], buf + (size_t)(w + k * NW) * 1024);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < KMAX; ++k) {
+        if (NI % NW != 0 && w + k * NW >= NI) break;  // wave-uniform
+        const int past = key[k] > last ? key[k] - last : 0;
+        dma16(base, off[k] - (uint32_t)(past * CPR * 16), buf + (size_t)(w + k * NW) * 1024);
+      }
+    }
+  }
+};
 // Issue this wave's share of one key tile: the tile is CPR*TK/64
 // wave-instructions, each moving 64 x 16 bytes straight into LDS (no VGPRs);
 // wave w issues instructions w, w+NW, ...  Keys past c1 read key c1-1
