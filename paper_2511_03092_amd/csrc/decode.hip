@@ -914,9 +914,13 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
     unsigned char* st = &stage[i % kLat8Stages][0];
     const int vb = kLat8Rows * (chunk + i * a.n_chunks);
     if (i == blk_new) {
+      // rows past the last valid one hold copies of it: where that is the new
+      // row, whose bytes in the cache are not written yet and may be NaN codes,
+      // they are overwritten too (their probabilities are 0, and 0 * NaN is not)
       if (has_new) {
-        const int r = vnew - vb;
-        *(u32x2*)(st + lat8_slot(r, tid() >> 1) * 16 + 8 * (tid() & 1)) = codes;
+        const int last = vnew == sp.nv - 1 ? kLat8Rows - 1 : vnew - vb;
+        for (int r = vnew - vb; r <= last; ++r)
+          *(u32x2*)(st + lat8_slot(r, tid() >> 1) * 16 + 8 * (tid() & 1)) = codes;
       }
       lat_barrier();
     }

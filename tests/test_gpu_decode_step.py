@@ -12,7 +12,7 @@ import torch
 
 import paper_2511_03092_amd as snap
 import synth
-from snaphelp import TOL, GpuCache, decode_steps, gpu_compress, params_of
+from snaphelp import TOL, GpuCache, decode_steps, gpu_compress, params_of, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -107,6 +107,16 @@ def test_step_latent_fp8_fused_kernel(hq, recent, topk, lengths):
         b = _fused_vs_two_calls(wl, p, lengths, [0, 1, 2], 3, 70, torch.bfloat16, invalid_slot=True)
         err = decode_steps(p, wl, b, [0, 1, 2], 4, torch.float32, TOL["fp8"], salt=7, fused="alt")
         print(f"  max abs err vs oracle: {err:.3e}", flush=True)
+
+
+@pytest.mark.parametrize("lengths", [[11, 700], [1, 63], [64, 65]])
+def test_step_latent_fp8_new_row_is_the_last(lengths):
+    """No kept rows: the new token's row is the last valid one and what follows it in its 64-row block must not reach the
+    output (cache rows that no token filled are NaN codes)."""
+    wl = synth.small(synth.WORKLOADS["mla-8head-61layer-b16-128k"], sink=6, recent=162, topk=0, kv_dtype="fp8")
+    p = params_of(wl)
+    _announce(f"decode_step fp8 latent, the new row the last one: lengths {lengths}")
+    run_case(wl, p, lengths, [1, 0], 2, 4, torch.float32, TOL["fp8"], fp8_scales=True, fused="alt")
 
 
 def test_step_fp8_fused_and_fp32_two_launch_paths():
