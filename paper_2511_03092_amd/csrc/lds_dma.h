@@ -11,24 +11,23 @@ namespace snap {
 // key k sits at slot k*CPR + (c ^ tile_swz<CPR>(k)).  The loads of a tile then
 // read contiguous memory (64 lanes cover whole rows; chunk by chunk, each load
 // instruction touched 64 cache lines), and a fragment read -- lane (l16, lg)
-// reads chunk 4t + lg of key l16 -- has distinct slots mod 16 over every 16
-// lanes that a 16-byte LDS read serves together (lanes 0-3, 12-15, 20-27 and
-// their like), so it is free of bank conflicts.  The chunk order 4t + lg is
-// part of that: with KSTEPS*lg + t, lanes of two groups meet in the same banks.
+// reads chunk CPR/4 * lg + t of key l16 -- has distinct slots mod 16 over every
+// 16 lanes that a 16-byte LDS read serves together (lanes 0-3, 12-15, 20-27 and
+// their like), so it is free of bank conflicts: the added 4 (or 2) puts keys 0-3
+// and 12-15 into one half of the slots and keys 4-11 into the other, whichever
+// of two neighbouring lane groups reads them.
 template <int CPR>
 __device__ __forceinline__ int tile_swz(int key) {
   static_assert(CPR % 8 == 0, "rows of whole 128-byte pieces");
-  return CPR % 16 == 0 ? key & 15 : (key >> 1) & 7;
+  return CPR % 16 == 0 ? (key + 4) & 15 : ((key >> 1) + 2) & 7;
 }
 template <int CPR>
 __device__ __forceinline__ int row_slot(int key, int c) { return key * CPR + (c ^ tile_swz<CPR>(key)); }
 
-// LDS tile of TK keys (64, or 32 for 576-wide rows) stored chunk-major: the
+// LDS tile of TK keys (576-wide rows, fp32 rows) stored chunk-major: the
 // 16-byte chunk c of key k sits at slot c*TK + k.  A fragment read by 16
 // consecutive keys of one chunk is 256 contiguous bytes, and every tile load
-// instruction covers 64 consecutive slots (lane i -> slot base + i).  (A
-// row-major tile with a swizzled chunk index, whose loads read contiguous
-// memory, measured slower for both row widths.)
+// instruction covers 64 consecutive slots (lane i -> slot base + i).
 template <int TK>
 __device__ __forceinline__ int tile_slot(int key, int c) { return c * TK + key; }
 

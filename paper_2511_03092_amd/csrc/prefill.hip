@@ -161,7 +161,7 @@ __global__ __launch_bounds__(512) void prefill_attn(PrefillArgs a) {
     prow[rb] = pos0 + po + l16;
   }
 
-  // query fragments: row l16 of each row block, chunks 4t + lg
+  // query fragments: row l16 of each row block, chunks KS*lg + t
   bf16x8 qf[2][KS];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(512) void prefill_attn(PrefillArgs a) {
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
       u32x4 x = {0u, 0u, 0u, 0u};
-      if (prow[rb] >= 0) x = *(const u32x4*)(qrow + 8 * (4 * t + lg));
+      if (prow[rb] >= 0) x = *(const u32x4*)(qrow + 8 * (KS * lg + t));
       qf[rb][t] = __builtin_bit_cast(bf16x8, x);
     }
   }
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(512) void prefill_attn(PrefillArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
         const bf16x8 kf =
-            __builtin_bit_cast(bf16x8, *(const u32x4*)(st + (size_t)row_slot<CPR>(kb * 16 + l16, 4 * t + lg) * 16));
+            __builtin_bit_cast(bf16x8, *(const u32x4*)(st + (size_t)row_slot<CPR>(kb * 16 + l16, KS * lg + t) * 16));
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) s[rb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[rb][t], s[rb][kb], 0, 0, 0);
       }
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(512) void prefill_attn(PrefillArgs a) {
         a.stats[(size_t)bg * a.rows_pad + rho] = make_float2(mc[rb], zt);
       uint16_t* qo = a.qobs + (((size_t)b * a.Hq + (size_t)g * a.G + hl[rb]) * a.w + ii) * D;
 #pragma unroll
-      for (int t = 0; t < KS; ++t) *(u32x4*)(qo + 8 * (4 * t + lg)) = __builtin_bit_cast(u32x4, qf[rb][t]);
+      for (int t = 0; t < KS; ++t) *(u32x4*)(qo + 8 * (KS * lg + t)) = __builtin_bit_cast(u32x4, qf[rb][t]);
     }
   }
   // rows of the score layout that no position fills: padding, and window rows
