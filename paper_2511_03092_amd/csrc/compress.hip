@@ -36,7 +36,7 @@ struct ScoreArgs {
   const float2* rowref; // [n_seq*Hkv][rows_pad]             (c, inv)
   float* A;             // [n_seq*Hkv][max_len]
   int Hq, Hkv, G, w, max_len, sink, recent, norm;
-  int rows, rows_pad, key_chunk, n_kchunks;
+  int rows, rows_pad, key_chunk, n_kchunks, groups;
   float scale;   // softmax scale
   float scale2;     // scale * log2(e) rounded to fp32 toward zero: logits in log2 units
   float scale2_lo;  // scale * log2(e) - scale2, > 0 (see split_scale2)
@@ -79,6 +79,26 @@ constexpr int kReadAhead = 4;
 
 // Products of sub-block sb (keys sb*16 .. sb*16+15 of the tile): acc[rb] holds
 // rows rb*16 + 4*(lane/16) + e (e = 0..3) against key sb*16 + lane%16.
+// Layout of a bf16 tile; lane group lg feeds chunk KSTEPS*lg + t of a key to
+// k-step t (the same for the queries): 64- and 128-wide keys row by row
+// (row_slot; 128-wide statistics pass of 8 ragged prompts 309 -> 278 us),
+// 576-wide ones chunk by chunk (row by row they took 878 instead of 681 us: the
+// addresses of 18 k-steps cost registers, and one workgroup per CU has the
+// whole L1 for a tile's lines).
+template <int KSTEPS, int TK>
+__device__ __forceinline__ int fragment_slot(int key, int t, int lg) {
+  return KSTEPS <= 4 ? row_slot<KSTEPS * 4>(key, KSTEPS * lg + t) : tile_slot<TK>(key, KSTEPS * lg + t);
+}
+
+// Sum over the four lanes l, l^16, l^32, l^48 by the lane-swap instructions (no
+// LDS round trip).
+__device__ __forceinline__ float lanes4_sum(float x) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
 template <typename In, int KSTEPS, int TK>
 __device__ __forceinline__ void score_mma_sb(const unsigned char* __restrict__ ktile, const bf16x8 (&qf)[2][KSTEPS],
                                              const float* qlds, int sb, int wave, int lane, bool wave_has_rows,
@@ -96,7 +116,7 @@ __device__ __forceinline__ void score_mma_sb(const unsigned char* __restrict__ k
     f32x4 odd[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int t = 0; t < KSTEPS; ++t) {
-      bf16x8 kf = __builtin_bit_cast(bf16x8, *(const u32x4*)(ktile + (size_t)tile_slot<TK>(key, KSTEPS * lg + t) * 16));
+      bf16x8 kf = __builtin_bit_cast(bf16x8, *(const u32x4*)(ktile + (size_t)fragment_slot<KSTEPS, TK>(key, t, lg) * 16));
       if (t & 1) {
         odd[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[0][t], kf, odd[0], 0, 0, 0);
         odd[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[1][t], kf, odd[1], 0, 0, 0);
@@ -175,8 +195,7 @@ __device__ __forceinline__ void score_epi_sb(const ScoreArgs& a, const f32x4 (&a
     }
     float cs = ((colv[0][0] + colv[0][1]) + (colv[0][2] + colv[0][3])) +
                ((colv[1][0] + colv[1][1]) + (colv[1][2] + colv[1][3]));
-    cs += __shfl_xor(cs, 16);
-    cs += __shfl_xor(cs, 32);
+    cs = lanes4_sum(cs);
     if (lg == 0) colbuf[wave * TK + sb * 16 + l16] = cs;
   }
 }
@@ -272,7 +291,11 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
 
   const int lane = tid() & 63, wave = tid() >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
-  const int bg = bid_y(), b = bg / a.Hkv, g = bg % a.Hkv;
+  // the column sums run in the reverse order of the statistics, so that what
+  // the last-level cache still holds of the keys is read first
+  const int bg = COLSUM ? a.groups - 1 - bid_y() : bid_y();
+  const int chunk = COLSUM ? a.n_kchunks - 1 - bid_x() : bid_x();
+  const int b = bg / a.Hkv, g = bg % a.Hkv;
   int L = uniform(a.lengths[b]);
   L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
   const int s = a.sink, r = a.recent;
@@ -285,7 +308,7 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
     lo = 0;
     hi = L;
   }
-  const int c0 = lo + bid_x() * a.key_chunk;
+  const int c0 = lo + chunk * a.key_chunk;
   int c1 = min(c0 + a.key_chunk, hi);
   if (!debug_check(c0 >= 0 && c1 <= a.max_len, kDbgScoreRange)) c1 = c0;  // skip the chunk
   const int we = min(a.w, L);
@@ -302,7 +325,7 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
       sl.rpos[rb][e] = L - a.w + ii;
     }
 
-  float2* st_out = a.stats + ((size_t)bg * a.n_kchunks + bid_x()) * a.rows_pad;
+  float2* st_out = a.stats + ((size_t)bg * a.n_kchunks + chunk) * a.rows_pad;
   if (c0 >= c1) {
     if (!COLSUM) {
       for (int t = tid(); t < a.rows_pad; t += nthreads()) st_out[t] = make_float2(-INFINITY, 0.f);
@@ -355,71 +378,58 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
   // later only add to the count, which makes those waits stricter).
   wait_vm<0>();
   const int nt = (c1 - c0 + TK - 1) / TK;  // tiles of this chunk
+  constexpr bool kRowMajor = kBF16 && KSTEPS <= 4;  // as fragment_slot
+  static_assert(!kRowMajor || STAGES == 2, "the ring loads chunk-major tiles");
   const int nload = tile_loads<CPR, NW, TK>(__builtin_amdgcn_readfirstlane(wave));
-  // prologue: tile 0 (the double buffer issues each next tile inside its
-  // loop), or the first STAGES-1 tiles of the ring
-  for (int st = 0; st < (STAGES == 2 ? 1 : STAGES - 1) && st < nt; ++st)
-    issue_tile<CPR, NW, TK>(kbase, kRowBytes, c0 + st * TK, c1, &tiles[st][0], wave, lane);
-
   // a tile is interior when all its keys are in range and precede the first
   // window position (rows of negative position exist only when L < w)
   const int first_row_pos = L - a.w;
   auto interior_of = [&](int t) { return t + TK <= c1 && t + TK - 1 <= first_row_pos; };
 
   if constexpr (STAGES == 2) {
-    // double buffer, unrolled by two (tile0 <- even tiles, tile1 <- odd
-    // tiles): the next tile is issued just before the current one is waited
-    // for.  Measured faster than the general ring for the small-row shapes.
-    constexpr int IPW = CPR * TK / 64 / NW;
-    static_assert(CPR * TK / 64 % NW == 0, "equal loads per wave");
-    unsigned char* tile0 = &tiles[0][0];
-    unsigned char* tile1 = &tiles[1][0];
+    TileLoad<CPR, NW, TK> tl;
+    if constexpr (kRowMajor) tl.init(wave, lane);
+    auto issue = [&](int t0, unsigned char* buf) {
+      if constexpr (kRowMajor)
+        tl.issue(kbase, t0, c1, buf);
+      else
+        issue_tile<CPR, NW, TK>(kbase, kRowBytes, t0, c1, buf, wave, lane);
+    };
+    issue(c0, &tiles[0][0]);
+    // Double buffer, one barrier per tile: past the barrier of a tile it has
+    // landed for every wave, and every wave is done with the tile before it,
+    // whose stage takes the next tile and whose column partials (the other
+    // colbuf half) are summed.
+    auto step = [&](int t0, int i, unsigned char* cur, unsigned char* nxt) {
+      wait_vm<0>();
+      lds_barrier();
+      if (t0 + TK < c1) issue(t0 + TK, nxt);
+      if constexpr (COLSUM) {
+        if (t0 > c0) colsum_finish<NW, TK>(a, colbuf[(i - 1) & 1], t0 - TK, c1, bg);
+      }
+      score_tile<In, KSTEPS, NW, COLSUM, TK>(a, cur, qf, qlds, colbuf[i & 1], sl, t0, c1, interior_of(t0), bg, wave,
+                                             lane, wave_has_rows);
+    };
     for (int t0 = c0; t0 < c1; t0 += 2 * TK) {
-      {
-        lds_barrier();  // every wave is done reading tile1
-        if (t0 + TK < c1) {
-          issue_tile<CPR, NW, TK>(kbase, kRowBytes, t0 + TK, c1, tile1, wave, lane);
-          wait_vm<IPW>();
-        } else {
-          wait_vm<0>();
-        }
-        lds_barrier();  // tile0 holds keys [t0, t0+TK)
-        score_tile<In, KSTEPS, NW, COLSUM, TK>(a, tile0, qf, qlds, colbuf[0], sl, t0, c1, interior_of(t0), bg,
-                                               wave, lane, wave_has_rows);
-        if constexpr (COLSUM) {
-          lds_barrier();
-          colsum_finish<NW, TK>(a, colbuf[0], t0, c1, bg);
-        }
-      }
-      const int t1 = t0 + TK;
-      if (t1 < c1) {
-        lds_barrier();  // every wave is done reading tile0
-        if (t1 + TK < c1) {
-          issue_tile<CPR, NW, TK>(kbase, kRowBytes, t1 + TK, c1, tile0, wave, lane);
-          wait_vm<IPW>();
-        } else {
-          wait_vm<0>();
-        }
-        lds_barrier();  // tile1 holds keys [t1, t1+TK)
-        score_tile<In, KSTEPS, NW, COLSUM, TK>(a, tile1, qf, qlds, colbuf[0], sl, t1, c1, interior_of(t1), bg,
-                                               wave, lane, wave_has_rows);
-        if constexpr (COLSUM) {
-          lds_barrier();
-          colsum_finish<NW, TK>(a, colbuf[0], t1, c1, bg);
-        }
-      }
+      step(t0, 0, &tiles[0][0], &tiles[1][0]);
+      if (t0 + TK < c1) step(t0 + TK, 1, &tiles[1][0], &tiles[0][0]);
+    }
+    if constexpr (COLSUM) {
+      lds_barrier();
+      colsum_finish<NW, TK>(a, colbuf[(nt - 1) & 1], c0 + (nt - 1) * TK, c1, bg);
     }
   } else {
     // Ring, one barrier per tile: past the barrier of tile i every wave has
     // finished tile i-1, so its stage takes tile i+STAGES-1 right away and
     // its column partials (the other colbuf half) can be summed.
+    for (int st = 0; st < STAGES - 1 && st < nt; ++st)
+      issue_tile<CPR, NW, TK>(kbase, kRowBytes, c0 + st * TK, c1, &tiles[st][0], wave, lane);
     for (int i = 0; i < nt; ++i) {
       wait_vm_dyn(min(nt - 1 - i, STAGES - 2) * nload);  // tile i has landed
       lds_barrier();                                      // ... for every wave
       const int t = c0 + i * TK;
       if (i + STAGES - 1 < nt)
-        issue_tile<CPR, NW, TK>(kbase, kRowBytes, t + (STAGES - 1) * TK, c1, &tiles[(i + STAGES - 1) % STAGES][0],
-                                wave, lane);
+        issue_tile<CPR, NW, TK>(kbase, kRowBytes, t + (STAGES - 1) * TK, c1, &tiles[(i + STAGES - 1) % STAGES][0], wave, lane);
       if constexpr (COLSUM) {
         if (i > 0) colsum_finish<NW, TK>(a, colbuf[(i - 1) & 1], t - TK, c1, bg);
       }
@@ -451,6 +461,206 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
         const int rho = wave * 32 + rb * 16 + lg * 4 + e;
         if (l16 == 0 && rho < a.rows_pad) st_out[rho] = make_float2(m, z);
       }
+  }
+}
+
+// ============================================================ streaming score passes
+// 64- and 128-wide bf16 keys.  Every wave holds all score rows of the group as
+// query fragments (RB blocks of 16 rows, RB * KS * 4 registers) and streams its
+// own blocks of 32 keys from memory into registers: no LDS and no barrier in
+// the loop, the next block in flight while one is scored.  The product is
+// S^T = K Q^T (A = 16 keys, B = 16 rows), so a lane holds one row of each block
+// against 4 * (lane / 16) + e of 16 keys: the row constants are one register
+// per block, a row's running (max, sum) is lane-local until the end, and the
+// column sums are an in-lane sum over the blocks and a reduction over 16 lanes.
+template <int N>
+__device__ __forceinline__ float row_ror_add(float x) {
+  const int r = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true);
+  return x + __int_as_float(r);
+}
+
+constexpr float kStatsLag = 8.f;  // log2 units the statistics' reference may lag a row's max
+
+template <int KS, int RB, bool COLSUM>
+__global__ __launch_bounds__(256) void score_stream(ScoreArgs a) {
+  constexpr int D = KS * 32;
+  constexpr int NW = 4;
+  __shared__ float2 part[COLSUM ? 1 : NW * RB * 16];
+  __shared__ int rpos[RB * 16];  // position of the row, or -1: not a row
+  const int lane = tid() & 63, wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  // the column sums run in the reverse order of the statistics, so that what
+  // the last-level cache still holds of the keys is read first
+  const int bg = COLSUM ? a.groups - 1 - bid_y() : bid_y();
+  const int chunk = COLSUM ? a.n_kchunks - 1 - bid_x() : bid_x();
+  const int b = bg / a.Hkv, g = bg % a.Hkv;
+  int L = uniform(a.lengths[b]);
+  L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
+  int lo = a.sink, hi = L - a.recent;
+  if (!COLSUM && a.norm != SNAP_NORM_CAND) {
+    lo = 0;
+    hi = L;
+  }
+  const int c0 = lo + chunk * a.key_chunk;
+  int c1 = min(c0 + a.key_chunk, hi);
+  if (!debug_check(c0 >= 0 && c1 <= a.max_len, kDbgScoreRange)) c1 = c0;  // skip the chunk
+  float2* st_out = a.stats + ((size_t)bg * a.n_kchunks + chunk) * a.rows_pad;
+  if (c0 >= c1) {
+    if (!COLSUM) {
+      for (int t = tid(); t < a.rows_pad; t += nthreads()) st_out[t] = make_float2(-INFINITY, 0.f);
+    }
+    return;
+  }
+  const int we = min(a.w, L);
+  const unsigned char* kbase =
+      (const unsigned char*)a.k + ((size_t)b * a.Hkv + g) * (size_t)a.max_len * (D * 2);
+
+  // 16 keys at t: this lane's chunks of key t + l16 (keys past c1 read key
+  // c1 - 1; they are masked)
+  auto load = [&](int t, u32x4 (&k)[KS]) {
+    const int j = min(t + l16, c1 - 1);
+    const unsigned char* p = kbase + (size_t)j * (D * 2) + lg * 16;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) k[s] = *(const u32x4*)(p + s * 64);
+  };
+  constexpr int kStep = 16 * NW;  // keys of one turn of the workgroup
+  int t = c0 + 16 * wave;
+  u32x4 k0[KS], k1[KS], k2[KS];
+  if (t < c1) load(t, k0);
+  if (t + kStep < c1) load(t + kStep, k1);
+
+  const uint16_t* qbase = (const uint16_t*)a.q + ((size_t)b * a.Hq + (size_t)g * a.G) * a.w * D;
+  bf16x8 qf[RB][KS];
+  float s0[RB], s1[RB];  // STATS: reference, sum; COLSUM: reference, 1/normaliser
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int rho = rb * 16 + l16;
+    const int ii = rho % a.w;
+    const bool ok = rho < a.rows && ii >= a.w - we;
+    if (wave == 0 && lg == 0) rpos[rho] = ok ? L - a.w + ii : -1;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (ok) v = *(const u32x4*)(qbase + (size_t)rho * D + 8 * (4 * s + lg));
+      qf[rb][s] = __builtin_bit_cast(bf16x8, v);
+    }
+    if (COLSUM) {
+      const float2 rf = ok ? a.rowref[(size_t)bg * a.rows_pad + rho] : make_float2(0.f, 0.f);
+      s0[rb] = rf.x;
+      s1[rb] = rf.y;
+    } else {
+      s0[rb] = -INFINITY;
+      s1[rb] = 0.f;
+    }
+  }
+  __syncthreads();  // rpos
+  const float s2 = a.scale2, s2lo = a.scale2_lo;
+  const int first_row_pos = L - a.w;
+
+  auto score = [&](int t, const u32x4 (&k)[KS]) {
+    // every key in range and before the first window position: nothing masked
+    const bool interior = t + 16 <= c1 && t + 15 <= first_row_pos;
+    float cs[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      // even and odd k-steps in chains of their own, summed at the end
+      f32x4 x = {0.f, 0.f, 0.f, 0.f}, od = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < KS; s += 2) {
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[s]), qf[rb][s], x, 0, 0, 0);
+        od = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[s + 1]), qf[rb][s + 1], od, 0, 0, 0);
+      }
+      x += od;
+      if constexpr (!COLSUM) {
+        if (!interior) {
+          const int rp = min(rpos[rb * 16 + l16], c1 - 1);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (t + 4 * lg + e > rp) x[e] = -INFINITY;
+        }
+        // the reference moves only when a term would pass 2^kStatsLag
+        const float mt = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) * s2;
+        if (wave_any(mt > s0[rb] + kStatsLag)) {
+          const float mn = fmaxf(s0[rb], mt);
+          s1[rb] *= fast_exp2(s0[rb] - (mn == -INFINITY ? 0.f : mn));
+          s0[rb] = mn;
+        }
+        const float mu = s0[rb] == -INFINITY ? 0.f : s0[rb];  // nothing seen yet: every term is 0
+        s1[rb] += (stats_term(x[0], s2, s2lo, mu) + stats_term(x[1], s2, s2lo, mu)) +
+                  (stats_term(x[2], s2, s2lo, mu) + stats_term(x[3], s2, s2lo, mu));
+      } else {
+        const float invl = s1[rb] * 0.69314718055994531f;
+        float wv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wv[e] = weight(x[e], s2, s2lo, s0[rb], s1[rb], invl);
+        if (!interior) {
+          const int rp = min(rpos[rb * 16 + l16], c1 - 1);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (t + 4 * lg + e > rp) wv[e] = 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[e] += wv[e];
+      }
+    }
+    if constexpr (COLSUM) {
+      // over the 16 rows of a block (lanes of equal lg); lane l16 = e < 4
+      // stores key 4lg + e
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        cs[e] = row_ror_add<8>(cs[e]);
+        cs[e] = row_ror_add<4>(cs[e]);
+        cs[e] = row_ror_add<2>(cs[e]);
+        cs[e] = row_ror_add<1>(cs[e]);
+      }
+      const float lo2 = (l16 & 1) ? cs[1] : cs[0], hi2 = (l16 & 1) ? cs[3] : cs[2];
+      const int j = t + 4 * lg + l16;
+      if (l16 < 4 && j < c1) a.A[(size_t)bg * a.max_len + j] = (l16 & 2) ? hi2 : lo2;
+    }
+  };
+
+  // three buffers in turn, two tiles in flight while one is scored
+  for (; t < c1; t += 3 * kStep) {
+    if (t + 2 * kStep < c1) load(t + 2 * kStep, k2);
+    score(t, k0);
+    if (t + kStep >= c1) break;
+    if (t + 3 * kStep < c1) load(t + 3 * kStep, k0);
+    score(t + kStep, k1);
+    if (t + 2 * kStep >= c1) break;
+    if (t + 4 * kStep < c1) load(t + 4 * kStep, k1);
+    score(t + 2 * kStep, k2);
+  }
+
+  if constexpr (!COLSUM) {
+    // a row's four lane groups, then the waves
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      float m = s0[rb], z = s1[rb];
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {
+        const float m2 = __shfl_xor(m, o), z2 = __shfl_xor(z, o);
+        const float mn = fmaxf(m, m2);
+        if (mn != -INFINITY) {
+          z = z * fast_exp2(m - mn) + z2 * fast_exp2(m2 - mn);
+          m = mn;
+        }
+      }
+      if (lg == 0) part[(wave * RB + rb) * 16 + l16] = make_float2(m, z);
+    }
+    __syncthreads();
+    for (int rho = tid(); rho < a.rows_pad; rho += nthreads()) {
+      float m = -INFINITY, z = 0.f;
+#pragma unroll
+      for (int w2 = 0; w2 < NW; ++w2) {
+        const float2 p = part[w2 * RB * 16 + rho];
+        const float mn = fmaxf(m, p.x);
+        if (mn != -INFINITY) {
+          z = z * fast_exp2(m - mn) + p.y * fast_exp2(p.x - mn);
+          m = mn;
+        }
+      }
+      st_out[rho] = make_float2(m, z);
+    }
   }
 }
 
@@ -1419,23 +1629,32 @@ Geometry compress_geometry(const snap_params& p, int n_seq, int max_len) {
   g.rows = G * p.obs_window;
   g.rows_pad = (g.rows + 31) / 32 * 32;
   int groups = n_seq * p.n_kv_heads;
-  // Key chunks: enough workgroups to cover the 256 CUs several times (about
-  // 4096), but each chunk at least 4 * rows_pad keys (16 * rows_pad for the
-  // wide latent groups, whose query block is 295 KB), so that its keys
-  // outweigh the query fragments every workgroup loads first (measured: the
-  // 256-row latent shape is fastest at 4096-key chunks; a single 128-row GQA
-  // prompt at 512-key chunks, 28% faster score passes than at 2048, and its
-  // compress call 4-8% faster than at 256).
-  long target = 4096;
-  long per_group = (target + groups - 1) / (groups > 0 ? groups : 1);
-  long kc = (max_len + per_group - 1) / (per_group > 0 ? per_group : 1);
-  const long kc_min = (g.rows_pad > 128 ? 16L : 4L) * g.rows_pad;
-  if (kc < kc_min) kc = kc_min;
-  kc = (kc + kKeyTile - 1) / kKeyTile * kKeyTile;
-  if (kc > 16384) kc = 16384;
-  g.key_chunk = (int)kc;
-  g.n_kchunks = (int)((max_len + kc - 1) / kc);
+  // Key chunks: enough workgroups to cover the 256 CUs several times, but each
+  // chunk several keys per score row, so that its keys outweigh the query
+  // fragments every workgroup loads first.  The 256-row latent shape (a query
+  // block of 295 KB) is fastest at 4096-key chunks.  64- and 128-wide keys:
+  // prompts of a batch differ in length, so a batch wants many short chunks, or
+  // CUs wait for the longest prompt's (8 ragged prompts padded to 128k, 64
+  // groups of 128 rows: statistics 278 us at 2048 keys, 267 at 1024, 274 at
+  // 512; column sums 310, 288, 268 -- the statistics also write a (max, sum)
+  // per row and chunk for stats_reduce, 10 / 13 / 28 us, so their chunks are
+  // longer).  A single 50k prompt: statistics 28 us at 512 keys, 32 at 384;
+  // column sums 35 and 29 us.
+  const bool latent = p.d_qk > 128, narrow = !latent && p.in_dtype == SNAP_BF16;
+  auto chunk = [&](long target, long least) {
+    const long per_group = (target + groups - 1) / (groups > 0 ? groups : 1);
+    long kc = (max_len + per_group - 1) / (per_group > 0 ? per_group : 1);
+    if (kc < least) kc = least;
+    kc = (kc + kKeyTile - 1) / kKeyTile * kKeyTile;
+    return (int)(kc > 16384 ? 16384 : kc);
+  };
+  const long rp = g.rows_pad;
+  g.key_chunk = narrow ? chunk(8192, rp > 64 ? 4 * rp : 256) : chunk(4096, (rp > 128 ? 16 : 4) * rp);
+  g.col_chunk = narrow && rp > 64 ? chunk(16384, 3 * rp) : g.key_chunk;
+  g.n_kchunks = (max_len + g.key_chunk - 1) / g.key_chunk;
+  g.n_colchunks = (max_len + g.col_chunk - 1) / g.col_chunk;
   if (g.n_kchunks < 1) g.n_kchunks = 1;
+  if (g.n_colchunks < 1) g.n_colchunks = 1;
   int ncand = max_len - p.sink - p.recent;
   if (ncand < 1) ncand = 1;
   g.n_splits = (ncand + kCandChunk - 1) / kCandChunk;
@@ -1492,10 +1711,25 @@ static hipError_t launch_score_nw(const ScoreArgs& sa, bool colsum, int groups, 
 // scored; 8% faster than two 64-key stages); 64/128-wide bf16 rows keep two
 // 64-key stages (three workgroups per CU; three or four stages measured
 // slower); fp32 rows 3 or 2 stages next to their fp32 query block.
+template <int KS>
+static hipError_t launch_stream(const ScoreArgs& sa, bool colsum, int groups, int n_kchunks, hipStream_t st) {
+  dim3 grid(n_kchunks, groups);
+  void (*k)(ScoreArgs);
+  if (sa.rows_pad <= 32)
+    k = colsum ? score_stream<KS, 2, true> : score_stream<KS, 2, false>;
+  else
+    k = colsum ? score_stream<KS, 4, true> : score_stream<KS, 4, false>;
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, sa);
+  return hipGetLastError();
+}
+
 template <typename In>
 static hipError_t launch_score(const ScoreArgs& sa, int dk, bool colsum, int groups, int n_kchunks, hipStream_t st) {
   const bool wide = sa.rows_pad > 128;
   if constexpr (sizeof(In) == 2) {
+    if (dk <= 128 && sa.rows_pad <= 64)
+      return dk == 64 ? launch_stream<2>(sa, colsum, groups, n_kchunks, st)
+                      : launch_stream<4>(sa, colsum, groups, n_kchunks, st);
     if (dk == 64) return wide ? launch_score_nw<In, 2, 8, 64, 2>(sa, colsum, groups, n_kchunks, st)
                               : launch_score_nw<In, 2, 4, 64, 2>(sa, colsum, groups, n_kchunks, st);
     if (dk == 128) return wide ? launch_score_nw<In, 4, 8, 64, 2>(sa, colsum, groups, n_kchunks, st)
@@ -1553,6 +1787,7 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
   sa.rows_pad = geo.rows_pad;
   sa.key_chunk = geo.key_chunk;
   sa.n_kchunks = geo.n_kchunks;
+  sa.groups = groups;
   sa.scale = scale;
   split_scale2(scale, sa.scale2, sa.scale2_lo);
   const bool bf = p.in_dtype == SNAP_BF16;
@@ -1591,8 +1826,10 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
                        stream, ra);
     if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
 
-    e = bf ? launch_score<uint16_t>(sa, p.d_qk, true, groups, geo.n_kchunks, stream)
-           : launch_score<float>(sa, p.d_qk, true, groups, geo.n_kchunks, stream);
+    sa.key_chunk = geo.col_chunk;
+    sa.n_kchunks = geo.n_colchunks;
+    e = bf ? launch_score<uint16_t>(sa, p.d_qk, true, groups, geo.n_colchunks, stream)
+           : launch_score<float>(sa, p.d_qk, true, groups, geo.n_colchunks, stream);
     if (e != hipSuccess) return SNAP_ERR_HIP;
 
     SelectArgs se;

@@ -169,8 +169,10 @@ struct Geometry {
   // compress
   int rows;         // G * obs_window
   int rows_pad;     // rows rounded up to 32 (one wave per 32 rows)
-  int key_chunk;    // keys per workgroup in the score passes
-  int n_kchunks;    // score-pass chunks per (sequence, KV head)
+  int key_chunk;    // keys per workgroup of the statistics pass
+  int n_kchunks;    // its chunks per (sequence, KV head)
+  int col_chunk;    // the same for the column-sum pass
+  int n_colchunks;
   int n_splits;     // candidate splits per group in pool/select
   int n_rowblocks;   // assemble row blocks per group
   size_t off_stats, off_rowref, off_A, off_P, off_hist, off_state, off_counts, off_sel, off_amax;
