@@ -12,15 +12,20 @@
 //                       the reset of the selection scratch
 //   score_pass<COLSUM>  recompute the scores, W = exp(z - c) * inv, column
 //                       sums over the G*w window rows -> A[j]
-//   pool_hist0          P = pool(A) over the candidates, histogram of the
-//                       first radix digit
-//   radix_scan x3       per (seq, KV head): pick the bin holding the K-th
-//                       largest P for the digit just counted
-//   radix_pass x2       histograms of the remaining digits (LDS per wave)
-//   select_count/write  ordered compaction: P > t, plus the lowest-index ties
+//   pool_hist           P = pool(A) over the candidates, histogram of their
+//                       leading bits
+//   select_refine       histogram of the next bits within the bin that holds
+//                       the K-th largest P
+//   select_collect      the candidates next to it are listed, those above
+//                       counted
+//   select_threshold    per (seq, KV head): the K-th largest P among the
+//                       listed ones
+//   band_rescore/decide fp64 scores next to the threshold, the final decision
+//   select_write        ordered compaction: P > t, plus the lowest-index ties
 //   assemble            sinks, ring rows, kept rows, zero padding (+ fp8)
 #include <float.h>
 #include <math.h>
+#include <string.h>
 
 #include "lds_dma.h"
 #include "snap_internal.h"
@@ -671,10 +676,11 @@ struct ReduceArgs {
   double2* rowz;       // [groups][rows_pad] (max in log2 units, sum of 2^(y - max)) in fp64
   int32_t* band_n;     // [groups] members of the re-score band (reset here)
   const int32_t* lengths;
-  uint32_t* hist;      // [3][groups][kRadixBins]
+  int32_t* list_n;     // [groups] listed candidates (reset here)
+  uint32_t* hist;      // [groups][kHistBins + kSubBins]
   RadixState* state;   // [groups]
   int groups, Hkv, max_len, sink, recent, topk;
-  int rows_pad, n_kchunks;
+  int rows_pad, n_kchunks, reset_wgs;  // reset_wgs: workgroups per group
 };
 
 // Row max m over every chunk and the normaliser, in log2 units (the stats
@@ -683,7 +689,7 @@ struct ReduceArgs {
 // directly, keeping the full fp32 accuracy of small logits), otherwise
 // c2 = m2; inv = 1 / sum_j 2^(y_j - c2), accumulated in fp64.  A wave owns a
 // row (chunks strided by 64, a few hundred at most) and combines with in-wave
-// shuffles; block 0 of each group also resets the group's selection scratch.
+// shuffles; the group's workgroups also reset its selection scratch.
 constexpr int kReduceLanes = 64;
 constexpr int kReduceRows = 256 / kReduceLanes;  // rows per workgroup
 __global__ __launch_bounds__(256) void stats_reduce(ReduceArgs a) {
@@ -721,11 +727,16 @@ __global__ __launch_bounds__(256) void stats_reduce(ReduceArgs a) {
       a.rowz[(size_t)bg * a.rows_pad + rho] = make_double2((double)m, z);
     }
   }
+  {
+    constexpr int kAll = kHistBins + kSubBins;
+    const int per = (kAll + a.reset_wgs - 1) / a.reset_wgs;
+    uint32_t* h = a.hist + (size_t)bg * kAll;
+    for (int i = bid_x() * per + tid(); i < min((bid_x() + 1) * per, kAll); i += nthreads()) h[i] = 0u;
+  }
   if (bid_x() != 0) return;
-  if (tid() == 0) a.band_n[bg] = 0;
-  for (int pass = 0; pass < 3; ++pass) {
-    uint32_t* h = a.hist + ((size_t)pass * a.groups + bg) * kRadixBins;
-    for (int i = tid(); i < kRadixBins; i += nthreads()) h[i] = 0u;
+  if (tid() == 0) {
+    a.band_n[bg] = 0;
+    a.list_n[bg] = 0;
   }
   if (tid() == 0) {
     int L = uniform(a.lengths[b]);
@@ -735,11 +746,10 @@ __global__ __launch_bounds__(256) void stats_reduce(ReduceArgs a) {
     int keff = n < a.topk ? n : a.topk;
     RadixState s;
     s.prefix = 0u;
-    s.mask = 0u;
     s.krem = keff;
     s.keff = keff;
     s.mode = keff == 0 ? 0 : (keff == n ? 1 : 2);
-    s.pad[0] = s.pad[1] = s.pad[2] = 0;
+    s.bin = s.sub = s.pad[0] = s.pad[1] = 0;
     a.state[bg] = s;
   }
 }
@@ -750,7 +760,9 @@ struct SelectArgs {
   float* P;              // [groups][max_len]
   float* pooled_out;     // optional [groups][max_len]
   const int32_t* lengths;
-  uint32_t* hist;        // [3][groups][kRadixBins]
+  uint32_t* hist;        // [groups][kHistBins + kSubBins]
+  uint2* list;           // [groups][kListCap] (score bits, token) of the candidates next to the K-th largest
+  int32_t* list_n;       // [groups] how many there are (more than kListCap: the list is not used)
   RadixState* state;     // [groups]
   uint2* counts;         // [groups][n_splits] (greater, equal)
   int32_t* sel;          // [groups][topk]
@@ -758,6 +770,7 @@ struct SelectArgs {
   int32_t* band_idx;     // [groups][kBandCap] their token indices (in arrival order)
   uint32_t* band_above;  // [groups][n_splits] candidates above the band per split
   int groups, Hkv, max_len, sink, recent, topk, pool_kernel, pool, n_splits;
+  uint32_t hist_top;     // leading bits of the largest score there can be (the number of score rows)
 };
 
 // The re-score band around the K-th largest pooled score tau (fp32 bits of a
@@ -776,7 +789,8 @@ __device__ __forceinline__ void band_limits(uint32_t tau_bits, uint32_t& lo, uin
 __device__ __forceinline__ RadixState load_state(const RadixState* p) {
   RadixState s = *p;
   s.prefix = (uint32_t)uniform((int)s.prefix);
-  s.mask = (uint32_t)uniform((int)s.mask);
+  s.bin = uniform(s.bin);
+  s.sub = uniform(s.sub);
   s.krem = uniform(s.krem);
   s.keff = uniform(s.keff);
   s.mode = uniform(s.mode);
@@ -792,137 +806,21 @@ __device__ __forceinline__ void seq_range(const SelectArgs& a, int bg, int& c0, 
   if (c1 < c0) c1 = c0;
 }
 
-// digit of pass d: bits [31:21], [20:10], [9:0]
-__device__ __forceinline__ uint32_t radix_digit(uint32_t bits, int pass) {
-  return pass == 0 ? (bits >> 21) : (pass == 1 ? ((bits >> 10) & 0x7ffu) : (bits & 0x3ffu));
+// Bin of a pooled score: its exponent and six bits of mantissa, the highest bin
+// for the largest score there can be (the number of score rows) and above, the
+// lowest for everything 64 octaves below that.
+__device__ __forceinline__ int hist_bin(uint32_t bits, uint32_t top) {
+  const int d = (int)(bits >> 17) - (int)top + (kHistBins - 1);
+  return d < 0 ? 0 : (d > kHistBins - 1 ? kHistBins - 1 : d);
 }
-__device__ __forceinline__ uint32_t radix_shift(int pass) { return pass == 0 ? 21u : (pass == 1 ? 10u : 0u); }
-__device__ __forceinline__ uint32_t radix_dmask(int pass) { return pass == 2 ? 0x3ffu : 0x7ffu; }
-
-// Each wave of a workgroup counts into its own LDS histogram (pooled scores of
-// neighbouring candidates share high bits, so one shared histogram would
-// serialise on a few bins); the four are summed and published with one
-// global atomic per non-empty bin.
-constexpr int kSubHists = kSelThreads / 64;
-__device__ __forceinline__ void radix_flush(const SelectArgs& a, int bg, int pass, uint32_t (*lhist)[kRadixBins]) {
-  const int nb = pass == 2 ? 1024 : 2048;
-  uint32_t* gh = a.hist + ((size_t)pass * a.groups + bg) * kRadixBins;
-  __syncthreads();
-  for (int i = tid(); i < nb; i += nthreads()) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int w = 0; w < kSubHists; ++w) v += lhist[w][i];
-    if (v) atomicAdd(&gh[i], v);
-  }
-}
-
-__device__ __forceinline__ void clear_hists(uint32_t (*lhist)[kRadixBins]) {
-  for (int i = tid(); i < kSubHists * kRadixBins; i += nthreads()) (&lhist[0][0])[i] = 0u;
-}
-
-// P = pool(A) on this workgroup's candidates (+ the debug copy) and the first
-// radix digit.
-__global__ __launch_bounds__(kSelThreads) void pool_hist0(SelectArgs a) {
-  __shared__ float la[kCandChunk + 64];
-  __shared__ uint32_t lhist[kSubHists][kRadixBins];
-  const int bg = bid_y(), split = bid_x();
-  const int wave = tid() >> 6;
-  int c0, c1;
-  seq_range(a, bg, c0, c1);
-  const int half = a.pool_kernel / 2;
-  const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
-  const RadixState st = load_state(&a.state[bg]);
-  float* Pg = a.P + (size_t)bg * a.max_len;
-
-  if (a.pooled_out && split == 0) {
-    float* po = a.pooled_out + (size_t)bg * a.max_len;
-    for (int j = tid(); j < a.max_len; j += nthreads())
-      if (j < c0 || j >= c1) po[j] = __uint_as_float(kQuietNaN);
-  }
-  if (st.mode == 2) clear_hists(lhist);
-  if (j0 < j1) {
-    const float* Ag = a.A + (size_t)bg * a.max_len;
-    const float padv = a.pool == SNAP_POOL_MAX ? -INFINITY : 0.f;
-    for (int i = tid(); i < (j1 - j0) + 2 * half; i += nthreads()) {
-      int t = j0 - half + i;
-      la[i] = (t >= c0 && t < c1) ? Ag[t] : padv;
-    }
-    __syncthreads();
-    for (int j = j0 + tid(); j < j1; j += nthreads()) {
-      const float* w = la + (j - j0);
-      float v;
-      if (a.pool == SNAP_POOL_MAX) {
-        v = w[0];
-        for (int t = 1; t < a.pool_kernel; ++t) v = fmaxf(v, w[t]);
-      } else {
-        v = 0.f;
-        for (int t = 0; t < a.pool_kernel; ++t) v += w[t];
-        v = v / (float)a.pool_kernel;
-      }
-      Pg[j] = v;
-      if (a.pooled_out) a.pooled_out[(size_t)bg * a.max_len + j] = v;
-      if (st.mode == 2) atomicAdd(&lhist[wave][radix_digit(__float_as_uint(v), 0)], 1u);
-    }
-  }
-  if (st.mode == 2) radix_flush(a, bg, 0, lhist);
-}
-
-__global__ __launch_bounds__(kSelThreads) void radix_pass(SelectArgs a, int pass) {
-  __shared__ uint32_t lhist[kSubHists][kRadixBins];
-  const int bg = bid_y(), split = bid_x();
-  const int wave = tid() >> 6;
-  const RadixState st = load_state(&a.state[bg]);
-  if (st.mode != 2) return;
-  int c0, c1;
-  seq_range(a, bg, c0, c1);
-  const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
-  clear_hists(lhist);
-  __syncthreads();
-  const float* Pg = a.P + (size_t)bg * a.max_len;
-  for (int j = j0 + tid(); j < j1; j += nthreads()) {
-    uint32_t bits = __float_as_uint(Pg[j]);
-    if ((bits & st.mask) == st.prefix) atomicAdd(&lhist[wave][radix_digit(bits, pass)], 1u);
-  }
-  radix_flush(a, bg, pass, lhist);
-}
-
-// One workgroup per group: find the bin that holds the krem-th largest of the
-// elements still matching the prefix, counting from the top bin down, and
-// narrow the threshold.  Thread t owns the 8 (or 4) bins just below the bins
-// of thread t-1, so its exclusive prefix is the count above its bins.
-__device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* lds, uint32_t& total);
-__global__ __launch_bounds__(kSelThreads) void radix_scan(SelectArgs a, int pass) {
-  __shared__ uint32_t lds[8];
-  const int bg = bid_x();
-  RadixState st = load_state(&a.state[bg]);
-  if (st.mode != 2) return;
-  const int nb = pass == 2 ? 1024 : 2048;
-  const int per = nb / kSelThreads;  // 8 or 4
-  const uint32_t* gh = a.hist + ((size_t)pass * a.groups + bg) * kRadixBins;
-  const int top = nb - per * tid();  // this thread's bins: [top - per, top)
-  uint32_t hv[8];
-  uint32_t tot = 0;
-  for (int i = 0; i < per; ++i) {
-    hv[i] = gh[top - 1 - i];
-    tot += hv[i];
-  }
-  uint32_t total;
-  const uint32_t above = block_exclusive_scan(tot, lds, total);
-  const uint32_t krem = (uint32_t)st.krem;
-  if (above < krem && above + tot >= krem) {
-    uint32_t cum = above;
-    for (int i = 0; i < per; ++i) {
-      if (cum + hv[i] >= krem) {
-        uint32_t bin = (uint32_t)(top - 1 - i);
-        st.krem -= (int32_t)cum;
-        st.prefix |= bin << radix_shift(pass);
-        st.mask |= radix_dmask(pass) << radix_shift(pass);
-        a.state[bg] = st;
-        break;
-      }
-      cum += hv[i];
-    }
-  }
+// The bit patterns [lo, hi] of a bin, and how far they are shifted down (from
+// lo) to their place among the bin's kSubBins parts: 6 bits, so that a part is
+// at most 2^-17 of its scores wide, except in the two end bins.
+__device__ __forceinline__ void bin_limits(int bin, uint32_t top, uint32_t& lo, uint32_t& hi, int& shift) {
+  const uint32_t first = (top - (kHistBins - 1) + (uint32_t)bin) << 17;
+  lo = bin == 0 ? 0u : first;
+  hi = bin == kHistBins - 1 ? 0xffffffffu : first | 0x1ffffu;
+  shift = 32 - __builtin_clz(hi - lo) - kSubBits;
 }
 
 // block-wide exclusive scan of one value per thread (lds holds one value per wave)
@@ -947,37 +845,345 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* lds, uint32_t& to
   return base + x - v;
 }
 
-constexpr int kPerThread = kCandChunk / kSelThreads;  // 8 consecutive candidates per thread
+constexpr int kPerThread = kCandChunk / kSelThreads;  // candidates per thread
 
-__global__ __launch_bounds__(kSelThreads) void select_count(SelectArgs a) {
-  __shared__ uint32_t lds[8];
+// P = pool(A) on this workgroup's candidates (+ the debug copy) and the
+// histogram of their bins.  Bins of 1.6% keep the pooled scores, which crowd
+// within an octave or two, from serialising on a few LDS counters, and the
+// lanes of a run with one bin (max pooling repeats a score over its window) add
+// once for the run, so one histogram serves the workgroup (three radix passes
+// with per-wave histograms of eight bins per octave, a scan launch each and a
+// count before this, select_refine, select_collect and select_threshold: 109 us
+// for 64 groups of up to 128k candidates, 41 us for 8 groups of 48k; now 52 and
+// 25 us).
+__global__ __launch_bounds__(kSelThreads) void pool_hist(SelectArgs a) {
+  __shared__ float la[kCandChunk + 64];
+  __shared__ uint32_t lhist[kHistBins];
   const int bg = bid_y(), split = bid_x();
-  const RadixState st = load_state(&a.state[bg]);
-  if (st.mode != 2) return;
+  const int lane = tid() & 63;
+  int c0, c1;
+  seq_range(a, bg, c0, c1);
+  const int half = a.pool_kernel / 2;
+  const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
+  const int mode = uniform(a.state[bg].mode);
+  float* Pg = a.P + (size_t)bg * a.max_len;
+
+  if (a.pooled_out && split == 0) {
+    float* po = a.pooled_out + (size_t)bg * a.max_len;
+    for (int j = tid(); j < a.max_len; j += nthreads())
+      if (j < c0 || j >= c1) po[j] = __uint_as_float(kQuietNaN);
+  }
+  if (j0 >= j1) return;
+  const float* Ag = a.A + (size_t)bg * a.max_len;
+  const float padv = a.pool == SNAP_POOL_MAX ? -INFINITY : 0.f;
+#pragma unroll 4
+  for (int i = tid(); i < (j1 - j0) + 2 * half; i += nthreads()) {
+    int t = j0 - half + i;
+    la[i] = (t >= c0 && t < c1) ? Ag[t] : padv;
+  }
+  if (mode == 2)
+    for (int i = tid(); i < kHistBins; i += nthreads()) lhist[i] = 0u;
+  __syncthreads();
+  for (int jj = j0; jj < j1; jj += nthreads()) {  // whole waves stay in the loop
+    const int j = jj + tid();
+    const bool in = j < j1;
+    float v = 0.f;
+    if (in) {
+      const float* w = la + (j - j0);
+      if (a.pool == SNAP_POOL_MAX) {
+        v = w[0];
+#pragma unroll 6
+        for (int t = 1; t < a.pool_kernel; ++t) v = fmaxf(v, w[t]);
+      } else {
+#pragma unroll 4
+        for (int t = 0; t < a.pool_kernel; ++t) v += w[t];
+        v = v / (float)a.pool_kernel;
+      }
+      Pg[j] = v;
+      if (a.pooled_out) a.pooled_out[(size_t)bg * a.max_len + j] = v;
+    }
+    if (mode == 2) {
+      const int d = in ? hist_bin(__float_as_uint(v), a.hist_top) : -1;
+      const int prev = __shfl_up(d, 1);
+      const bool start = lane == 0 || prev != d;
+      const uint64_t starts = __builtin_amdgcn_ballot_w64(start);
+      const uint64_t after = lane == 63 ? 0 : starts >> (lane + 1);
+      const int run = after ? __builtin_ctzll(after) + 1 : 64 - lane;
+      if (start && in) atomicAdd(&lhist[d], (uint32_t)run);
+    }
+  }
+  if (mode != 2) return;
+  __syncthreads();
+  uint32_t* gh = a.hist + (size_t)bg * (kHistBins + kSubBins);
+  for (int i = tid(); i < kHistBins; i += nthreads()) {
+    const uint32_t v = lhist[i];
+    if (v) atomicAdd(&gh[i], v);
+  }
+}
+
+// Bin of the want-th largest entry of the histogram h[NB] (counted from the top
+// bin down), and what is left of `want` within it.  Thread t owns the bins just
+// below those of thread t-1, so its exclusive prefix is the count above its
+// bins.  Every thread of the workgroup (kSelThreads) calls it and gets the
+// result; it holds two barriers after pick is written.
+template <int NB>
+__device__ __forceinline__ int find_bin(const uint32_t* h, uint32_t& want, uint32_t* lds, uint32_t* pick) {
+  constexpr int kBins = NB / kSelThreads;
+  const u32x4* gh = (const u32x4*)(h + (NB - kBins * (tid() + 1)));
+  u32x4 hv[kBins / 4];
+  uint32_t tot = 0, total;
+#pragma unroll
+  for (int i = 0; i < kBins / 4; ++i) {
+    hv[i] = gh[i];
+    tot += (hv[i][0] + hv[i][1]) + (hv[i][2] + hv[i][3]);
+  }
+  const uint32_t above = block_exclusive_scan(tot, lds, total);
+  if (above < want && above + tot >= want) {
+    uint32_t cum = above;
+    bool done = false;
+#pragma unroll
+    for (int i = kBins - 1; i >= 0; --i) {
+      const uint32_t c = hv[i >> 2][i & 3];
+      if (!done && cum + c >= want) {
+        pick[0] = (uint32_t)(NB - kBins * (tid() + 1) + i);
+        pick[1] = want - cum;
+        done = true;
+      }
+      cum += c;
+    }
+  }
+  __syncthreads();
+  const int bin = uniform((int)pick[0]);
+  want = (uint32_t)uniform((int)pick[1]);
+  __syncthreads();
+  return bin;
+}
+
+// Every workgroup finds the bin that holds the K_eff-th largest score for
+// itself (16 KB of counts from the L2: about what a launch of its own would
+// take), then counts its candidates of that bin in kSubBins parts.
+__global__ __launch_bounds__(kSelThreads) void select_refine(SelectArgs a) {
+  __shared__ uint32_t lds[8], pick[2];
+  __shared__ uint32_t lhist[kSubBins];
+  const int bg = bid_y(), split = bid_x();
+  if (uniform(a.state[bg].mode) != 2) return;
+  uint32_t want = (uint32_t)uniform(a.state[bg].keff);
   int c0, c1;
   seq_range(a, bg, c0, c1);
   const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
+  if (j0 >= j1) return;  // never split 0: there are candidates
   const float* Pg = a.P + (size_t)bg * a.max_len;
-  uint32_t lo, hi;
-  band_limits(st.prefix, lo, hi);
-  uint32_t gt = 0, eq = 0, above = 0;
-  for (int j = j0 + tid(); j < j1; j += nthreads()) {
-    uint32_t bits = __float_as_uint(Pg[j]);
-    gt += bits > st.prefix;
-    eq += bits == st.prefix;
-    above += bits > hi;
-    if (bits >= lo && bits <= hi) {
-      const int m = atomicAdd(&a.band_n[bg], 1);
-      if (m < kBandCap) a.band_idx[(size_t)bg * kBandCap + m] = j;
-    }
+  uint32_t bits[kPerThread];
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) bits[i] = __float_as_uint(Pg[min(j0 + tid() + i * kSelThreads, j1 - 1)]);
+  for (int i = tid(); i < kSubBins; i += nthreads()) lhist[i] = 0u;
+  uint32_t* gh = a.hist + (size_t)bg * (kHistBins + kSubBins);
+  const int bin = find_bin<kHistBins>(gh, want, lds, pick);
+  if (split == 0 && tid() == 0) {
+    a.state[bg].bin = bin;
+    a.state[bg].krem = (int32_t)want;
   }
-  uint32_t tg, te, ta;
-  block_exclusive_scan(gt, lds, tg);
-  block_exclusive_scan(eq, lds, te);
-  block_exclusive_scan(above, lds, ta);
+  uint32_t lo, hi;
+  int shift;
+  bin_limits(bin, a.hist_top, lo, hi, shift);
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i)
+    if (j0 + tid() + i * kSelThreads < j1 && bits[i] >= lo && bits[i] <= hi)
+      atomicAdd(&lhist[(bits[i] - lo) >> shift], 1u);
+  __syncthreads();
+  for (int i = tid(); i < kSubBins; i += nthreads()) {
+    const uint32_t v = lhist[i];
+    if (v) atomicAdd(&gh[kHistBins + i], v);
+  }
+}
+
+// The scores that can decide the threshold when it lies in part `sub` of `bin`,
+// as bit patterns: that part's, and as far on each side as the re-score band of
+// any of them reaches (2^-17 of the score; twice that here).
+__device__ __forceinline__ void list_limits(int bin, int sub, uint32_t top, uint32_t& lo, uint32_t& hi) {
+  uint32_t blo, bhi;
+  int shift;
+  bin_limits(bin, top, blo, bhi, shift);
+  const uint32_t first = blo + ((uint32_t)sub << shift), last = first + ((1u << shift) - 1u);
+  lo = __float_as_uint(__uint_as_float(first) * (1.0f - 2.f * kBandRel));
+  hi = last >= 0x7f800000u || last < first ? 0xffffffffu : __float_as_uint(__uint_as_float(last) * (1.0f + 2.f * kBandRel));
+  if (first >= 0x7f800000u) lo = first;  // not finite: no band
+}
+
+// Every workgroup finds the part of the bin that holds the threshold, lists its
+// candidates next to it and counts those above.
+__global__ __launch_bounds__(kSelThreads) void select_collect(SelectArgs a) {
+  __shared__ uint32_t lds[8], pick[2];
+  __shared__ uint2 buf[kCandChunk];
+  __shared__ int nbuf, base;
+  const int bg = bid_y(), split = bid_x();
+  if (uniform(a.state[bg].mode) != 2) return;
+  int c0, c1;
+  seq_range(a, bg, c0, c1);
+  const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
+  if (j0 >= j1) {
+    if (tid() == 0) {
+      a.counts[(size_t)bg * a.n_splits + split] = make_uint2(0u, 0u);
+      a.band_above[(size_t)bg * a.n_splits + split] = 0u;
+    }
+    return;
+  }
+  const int bin = uniform(a.state[bg].bin);
+  uint32_t want = (uint32_t)uniform(a.state[bg].krem);
+  const float* Pg = a.P + (size_t)bg * a.max_len;
+  uint32_t bits[kPerThread];
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) bits[i] = __float_as_uint(Pg[min(j0 + tid() + i * kSelThreads, j1 - 1)]);
+  if (tid() == 0) nbuf = 0;
+  const int sub = find_bin<kSubBins>(a.hist + (size_t)bg * (kHistBins + kSubBins) + kHistBins, want, lds, pick);
+  uint32_t lo, hi;
+  list_limits(bin, sub, a.hist_top, lo, hi);
+  uint32_t above = 0;
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) {
+    const int j = j0 + tid() + i * kSelThreads;
+    if (j >= j1) continue;
+    above += bits[i] > hi;
+    if (bits[i] >= lo && bits[i] <= hi) buf[atomicAdd(&nbuf, 1)] = make_uint2(bits[i], (uint32_t)j);
+  }
+  uint32_t ta;
+  block_exclusive_scan(above, lds, ta);  // its barriers also complete buf
   if (tid() == 0) {
-    a.counts[(size_t)bg * a.n_splits + split] = make_uint2(tg, te);
+    a.counts[(size_t)bg * a.n_splits + split] = make_uint2(ta, 0u);
     a.band_above[(size_t)bg * a.n_splits + split] = ta;
+    if (split == 0) a.state[bg].sub = sub;
+    base = nbuf ? atomicAdd(&a.list_n[bg], nbuf) : 0;
+  }
+  __syncthreads();
+  for (int i = tid(); i < nbuf; i += nthreads())
+    if (base + i < kListCap) a.list[(size_t)bg * kListCap + base + i] = buf[i];
+}
+
+// One workgroup per group: the K_eff-th largest score among those within the
+// list's limits (a radix select in LDS, digits of 8 bits below the highest bit in
+// which the limits differ: 10 bits, except in the end bins), then the exact
+// counts per split and the members of the re-score band.  A group with more such
+// candidates than the list holds (many equal scores) reads all its scores
+// instead, kThrU a thread in flight.
+constexpr int kThrThreads = 512;
+constexpr int kThrBits = 8;
+constexpr int kThrU = 8;
+__global__ __launch_bounds__(kThrThreads) void select_threshold(SelectArgs a) {
+  __shared__ uint2 list[kListCap];
+  __shared__ uint32_t cnt[1 << kThrBits];
+  __shared__ uint32_t lds[kThrThreads / 64];
+  __shared__ uint32_t pick[2];
+  __shared__ int nband;
+  const int bg = bid_x();
+  RadixState st = load_state(&a.state[bg]);
+  if (st.mode != 2) return;
+  int c0, c1;
+  seq_range(a, bg, c0, c1);
+  const float* Pg = a.P + (size_t)bg * a.max_len;
+  uint2* counts = a.counts + (size_t)bg * a.n_splits;
+  uint32_t* band_above = a.band_above + (size_t)bg * a.n_splits;
+  const int n = uniform(a.list_n[bg]), lane = tid() & 63;
+  const bool listed = n <= kListCap;
+  uint32_t lo, hi;
+  list_limits(st.bin, st.sub, a.hist_top, lo, hi);
+  if (listed)
+    for (int i = tid(); i < n; i += nthreads()) list[i] = a.list[(size_t)bg * kListCap + i];
+  uint32_t above = 0, total;
+  for (int s = tid(); s < a.n_splits; s += nthreads()) above += band_above[s];
+  if (tid() == 0) nband = 0;
+  block_exclusive_scan(above, lds, total);
+  uint32_t want = (uint32_t)st.keff - total;
+  // fn(score bits, token) for every candidate within the limits; whole waves
+  // call it (in = false: nothing)
+  auto each = [&](auto fn) {
+    if (listed) {
+      for (int i0 = 0; i0 < n; i0 += nthreads()) {
+        const int i = i0 + tid();
+        const uint2 e = i < n ? list[i] : make_uint2(0u, 0u);
+        fn(i < n, e.x, (int)e.y);
+      }
+    } else {
+      for (int j0 = c0; j0 < c1; j0 += kThrU * kThrThreads) {
+        uint32_t bits[kThrU];
+#pragma unroll
+        for (int u = 0; u < kThrU; ++u) bits[u] = __float_as_uint(Pg[min(j0 + u * kThrThreads + tid(), c1 - 1)]);
+#pragma unroll
+        for (int u = 0; u < kThrU; ++u) {
+          const int j = j0 + u * kThrThreads + tid();
+          fn(j < c1 && bits[u] >= lo && bits[u] <= hi, bits[u], j);
+        }
+      }
+    }
+  };
+  // largest first: digit 0 is the highest score's
+  uint32_t prefix = 0;
+  int shift = 32 - __builtin_clz(hi - lo);  // bits of hi - score still to decide
+  while (shift > 0) {
+    const int w = shift < kThrBits ? shift : kThrBits;
+    const int below = shift - w;
+    if (tid() < (1 << kThrBits)) cnt[tid()] = 0u;
+    __syncthreads();
+    each([&](bool in, uint32_t bits, int) {
+      const uint32_t r = hi - bits;
+      in = in && (shift == 32 || (r >> shift) == (prefix >> shift));
+      const uint32_t d = (r >> below) & ((1u << w) - 1u);
+      // equal scores of a wave count once for all
+      const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+      if (m == 0) return;
+      const int first = __builtin_ctzll(m);
+      const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+      const uint64_t same = __builtin_amdgcn_ballot_w64(in && d == d0);
+      if (lane == first) atomicAdd(&cnt[d0], (uint32_t)__builtin_popcountll(same));
+      if (in && d != d0) atomicAdd(&cnt[d], 1u);
+    });
+    __syncthreads();
+    const uint32_t mine = tid() < (1 << kThrBits) ? cnt[tid()] : 0u;
+    const uint32_t before = block_exclusive_scan(mine, lds, total);
+    if (before < want && before + mine >= want) {
+      pick[0] = (uint32_t)tid();
+      pick[1] = before;
+    }
+    __syncthreads();
+    prefix |= pick[0] << below;
+    want -= pick[1];
+    shift = below;
+    __syncthreads();
+  }
+  const uint32_t tau = hi - prefix;
+  uint32_t blo, bhi;
+  band_limits(tau, blo, bhi);
+  each([&](bool in, uint32_t bits, int j) {
+    const int s = (j - c0) / kCandChunk;
+    const bool gt = in && bits > tau, eq = in && bits == tau, up = in && bits > bhi;
+    if (listed) {
+      if (gt) atomicAdd(&counts[s].x, 1u);
+      if (eq) atomicAdd(&counts[s].y, 1u);
+      if (up) atomicAdd(&band_above[s], 1u);
+    } else {
+      // 64 consecutive candidates, a multiple of 64 from the first: one split
+      const uint64_t mg = __builtin_amdgcn_ballot_w64(gt), me = __builtin_amdgcn_ballot_w64(eq),
+                     mu = __builtin_amdgcn_ballot_w64(up);
+      if (lane == 0) {
+        if (mg) atomicAdd(&counts[s].x, (uint32_t)__builtin_popcountll(mg));
+        if (me) atomicAdd(&counts[s].y, (uint32_t)__builtin_popcountll(me));
+        if (mu) atomicAdd(&band_above[s], (uint32_t)__builtin_popcountll(mu));
+      }
+    }
+    const bool member = in && bits >= blo && bits <= bhi;
+    const uint64_t mm = __builtin_amdgcn_ballot_w64(member);
+    if (mm == 0) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&nband, (int)__builtin_popcountll(mm));
+    base = uniform(base);
+    const int m = base + (int)__builtin_popcountll(mm & ((1ull << lane) - 1ull));
+    if (member && m < kBandCap) a.band_idx[(size_t)bg * kBandCap + m] = j;
+  });
+  __syncthreads();
+  if (tid() == 0) {
+    a.band_n[bg] = nband;
+    st.prefix = tau;
+    st.krem = (int32_t)want;
+    a.state[bg] = st;
   }
 }
 
@@ -1017,6 +1223,7 @@ struct BandArgs {
 __device__ __forceinline__ int token_rank(const int32_t* s, int nb, int i) {
   const int32_t x = s[i];
   int r = 0;
+#pragma unroll 8
   for (int u = 0; u < nb; ++u) r += s[u] < x;
   return r;
 }
@@ -1066,7 +1273,6 @@ __device__ __forceinline__ int band_key_token(const int32_t* tok, const int32_t*
   return t0 + (x - first[lo]);
 }
 
-constexpr int kBandWGs = 16;       // band_rescore workgroups per group (work items strided over them)
 constexpr int kBandKeys = 4;       // keys per block (staged in LDS together)
 constexpr int kBandThreads = 512;  // rows x slices of the query dims
 constexpr int kBandKeyCap = 1024;  // band keys per group; more keeps the fp32 selection
@@ -1200,6 +1406,7 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
   __shared__ int32_t sj[kBandCap];
   __shared__ int32_t tok[kBandCap];
   __shared__ int32_t first[kBandCap + 1];
+  __shared__ double key_A[kBandKeyCap];
   __shared__ uint32_t lds[8];
   const int bg = bid_x();
   RadixState st = load_state(&a.state[bg]);
@@ -1212,7 +1419,22 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
   const int c0 = a.sink, c1 = L - a.recent, half = a.pool_kernel / 2;
   for (int i = tid(); i < nb; i += nthreads()) sj[i] = a.band_idx[(size_t)bg * kBandCap + i];
   __syncthreads();
-  if (band_keys(sj, nb, half, c0, c1, tok, first, lds) > kBandKeyCap) return;  // as band_rescore
+  const int nkeys = band_keys(sj, nb, half, c0, c1, tok, first, lds);
+  if (nkeys > kBandKeyCap) return;  // as band_rescore
+  // the keys' A from their row passes, all loads in flight together (a thread
+  // that gathered a member's window from memory waited for each of its keys)
+  {
+    const double* Ag = a.A64 + (size_t)bg * kBandKeyCap * kBandMaxPass;
+    const int npass = (a.rows_pad + a.rows_per_pass - 1) / a.rows_per_pass;
+    for (int x = tid(); x < nkeys; x += nthreads()) {
+      double part[kBandMaxPass], At = 0.0;
+#pragma unroll
+      for (int pp = 0; pp < kBandMaxPass; ++pp) part[pp] = pp < npass ? Ag[(size_t)x * kBandMaxPass + pp] : 0.0;
+#pragma unroll
+      for (int pp = 0; pp < kBandMaxPass; ++pp) At += part[pp];
+      key_A[x] = At;
+    }
+  }
   uint32_t lo, hi;
   band_limits(st.prefix, lo, hi);
   // candidates above the band (all kept)
@@ -1222,8 +1444,6 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
   block_exclusive_scan(above, lds, n_above);
   const int need = st.keff - (int)n_above;  // in [1, nb] (tau itself is a member)
   if (need < 0 || need > nb) return;         // not for finite scores; the fp32 selection stands
-  const double* Ag = a.A64 + (size_t)bg * kBandKeyCap * kBandMaxPass;
-  const int npass = (a.rows_pad + a.rows_per_pass - 1) / a.rows_per_pass;
   for (int i = tid(); i < nb; i += nthreads()) {
     const int j = sj[i];
     const int t0 = max(j - half, c0), t1 = min(j + half, c1 - 1);
@@ -1238,9 +1458,7 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
       }
       int k0 = max(tok[lo] - half, c0);
       if (lo > 0) k0 = max(k0, tok[lo - 1] + half + 1);
-      const int x = first[lo] + (t - k0);
-      double At = 0.0;
-      for (int pp = 0; pp < npass; ++pp) At += Ag[(size_t)x * kBandMaxPass + pp];
+      const double At = key_A[first[lo] + (t - k0)];
       if (a.pool == SNAP_POOL_MAX)
         pooled = At > pooled ? At : pooled;
       else
@@ -1258,17 +1476,19 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
     const double pi = sp[i];
     const int ji = sj[i];
     int r = 0;
+#pragma unroll 4
     for (int u = 0; u < nb; ++u) r += sp[u] > pi || (sp[u] == pi && sj[u] < ji);
     tok[i] = r < need;
   }
   __syncthreads();
   // per-split counts of what the compaction keeps: the candidates above the
   // band and the kept members
-  for (int s = tid(); s < a.n_splits; s += nthreads()) {
-    uint32_t n = a.band_above[(size_t)bg * a.n_splits + s];
-    for (int i = 0; i < nb; ++i) n += tok[i] && (sj[i] - c0) / kCandChunk == s;
-    a.counts[(size_t)bg * a.n_splits + s] = make_uint2(n, 0u);
-  }
+  uint2* counts = a.counts + (size_t)bg * a.n_splits;
+  for (int s = tid(); s < a.n_splits; s += nthreads())
+    counts[s] = make_uint2(a.band_above[(size_t)bg * a.n_splits + s], 0u);
+  __syncthreads();
+  for (int i = tid(); i < nb; i += nthreads())
+    if (tok[i]) atomicAdd(&counts[(sj[i] - c0) / kCandChunk].x, 1u);
   for (int i = tid(); i < nb; i += nthreads()) Pg[sj[i]] = __uint_as_float(tok[i] ? hi + 1u : 0u);
   if (tid() == 0) {
     st.prefix = hi;
@@ -1278,64 +1498,78 @@ __global__ __launch_bounds__(kSelThreads) void band_decide(BandArgs a) {
 }
 
 // Ordered compaction: a candidate is kept when P > t, or P == t and it is among
-// the krem lowest-index candidates equal to t.  Output is in token order.
+// the krem lowest-index candidates equal to t, and goes to place (candidates
+// above t before it) + min(candidates equal to t before it, krem): token order.
+// A wave takes 512 consecutive candidates, 64 a load, and counts them by ballot,
+// so the workgroup meets once (with 8 candidates in a row per thread, 32-byte
+// strides, four block scans and a serial sum over the splits before it, 19 us
+// for 64 groups of up to 128k candidates).
 __global__ __launch_bounds__(kSelThreads) void select_write(SelectArgs a) {
-  __shared__ uint32_t lds[8];
+  constexpr int kWaves = kSelThreads / 64, kWaveCands = kCandChunk / kWaves;
+  __shared__ uint2 wcnt[kWaves], before[kWaves];
   const int bg = bid_y(), split = bid_x();
-  const RadixState st = load_state(&a.state[bg]);
-  if (st.mode == 0) return;
+  const int lane = tid() & 63, wave = uniform(tid() >> 6);
   int c0, c1;
   seq_range(a, bg, c0, c1);
   const int j0 = c0 + split * kCandChunk, j1 = min(j0 + kCandChunk, c1);
+  if (j0 >= j1) return;
+  const float* Pg = a.P + (size_t)bg * a.max_len;
+  const int jw = j0 + wave * kWaveCands + lane;
+  uint32_t bits[kWaveCands / 64];
+#pragma unroll
+  for (int i = 0; i < kWaveCands / 64; ++i) bits[i] = __float_as_uint(Pg[min(jw + 64 * i, j1 - 1)]);
+  uint32_t gb = 0, eb = 0;  // candidates above / equal in the splits before this one
+  for (int t = tid(); t < split; t += nthreads()) {
+    const uint2 c = a.counts[(size_t)bg * a.n_splits + t];
+    gb += c.x;
+    eb += c.y;
+  }
+  const RadixState st = load_state(&a.state[bg]);
+  if (st.mode == 0) return;
   int32_t* sg = a.sel + (size_t)bg * a.topk;
   if (st.mode == 1) {
     for (int j = j0 + tid(); j < j1; j += nthreads()) sg[j - c0] = j;
     return;
   }
-  uint32_t gt_before = 0, eq_before = 0;
-  for (int t = 0; t < split; ++t) {
-    uint2 c = a.counts[(size_t)bg * a.n_splits + t];
-    gt_before += c.x;
-    eq_before += c.y;
-  }
-  const uint32_t krem = (uint32_t)st.krem;
-  const uint32_t ties_here = krem > eq_before ? krem - eq_before : 0u;
-  const uint32_t out_base = gt_before + (eq_before < krem ? eq_before : krem);
-  const float* Pg = a.P + (size_t)bg * a.max_len;
-  const int jt = j0 + tid() * kPerThread;
-  uint32_t bits[kPerThread];
-  uint32_t neq = 0;
+  uint64_t gt[kWaveCands / 64], eq[kWaveCands / 64];
+  uint32_t ng = 0, ne = 0;
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {
-    int j = jt + i;
-    bits[i] = j < j1 ? __float_as_uint(Pg[j]) : 0u;
-    neq += (j < j1 && bits[i] == st.prefix);
+  for (int i = 0; i < kWaveCands / 64; ++i) {
+    const bool in = jw + 64 * i < j1;
+    gt[i] = __builtin_amdgcn_ballot_w64(in && bits[i] > st.prefix);
+    eq[i] = __builtin_amdgcn_ballot_w64(in && bits[i] == st.prefix);
+    ng += (uint32_t)__builtin_popcountll(gt[i]);
+    ne += (uint32_t)__builtin_popcountll(eq[i]);
   }
-  uint32_t tot;
-  uint32_t eq_rank = block_exclusive_scan(neq, lds, tot);
-  bool keep[kPerThread];
-  uint32_t nkeep = 0;
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {
-    int j = jt + i;
-    bool in = j < j1;
-    bool k = false;
-    if (in && bits[i] > st.prefix) k = true;
-    if (in && bits[i] == st.prefix) {
-      k = eq_rank < ties_here;
-      ++eq_rank;
-    }
-    keep[i] = k;
-    nkeep += k;
+  for (int o = 32; o >= 1; o >>= 1) {
+    gb += (uint32_t)__shfl_xor((int)gb, o);
+    eb += (uint32_t)__shfl_xor((int)eb, o);
   }
-  uint32_t pos = out_base + block_exclusive_scan(nkeep, lds, tot);
-  const uint32_t keff = (uint32_t)st.keff;
+  if (lane == 0) {
+    wcnt[wave] = make_uint2(ng, ne);
+    before[wave] = make_uint2(gb, eb);
+  }
+  __syncthreads();
+  uint32_t G = 0, E = 0;
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i)
-    if (keep[i]) {
-      if (debug_check(pos < keff, kDbgSelWrite) && pos < keff) sg[pos] = jt + i;  // never past the group's K slots
-      ++pos;
-    }
+  for (int w = 0; w < kWaves; ++w) {
+    G += before[w].x + (w < wave ? wcnt[w].x : 0u);
+    E += before[w].y + (w < wave ? wcnt[w].y : 0u);
+  }
+  const uint32_t krem = (uint32_t)st.krem, keff = (uint32_t)st.keff;
+  const uint64_t lower = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < kWaveCands / 64; ++i) {
+    const uint32_t g = G + (uint32_t)__builtin_popcountll(gt[i] & lower);
+    const uint32_t e = E + (uint32_t)__builtin_popcountll(eq[i] & lower);
+    const bool keep = (gt[i] >> lane & 1) || ((eq[i] >> lane & 1) && e < krem);
+    const uint32_t pos = g + (e < krem ? e : krem);
+    // never past the group's K slots
+    if (keep && debug_check(pos < keff, kDbgSelWrite) && pos < keff) sg[pos] = jw + 64 * i;
+    G += (uint32_t)__builtin_popcountll(gt[i]);
+    E += (uint32_t)__builtin_popcountll(eq[i]);
+  }
 }
 
 // ============================================================ assemble
@@ -1358,6 +1592,7 @@ struct AssembleArgs {
 };
 
 constexpr int kAsmRows = 64;  // cache rows per assemble workgroup
+constexpr int kAsmU = 8;      // row pieces a thread has in flight
 
 // First ring token l0 = max(L - r, s) and ring_base = (l0 - s) mod r, the
 // ring row of token l0 counted from s (one division per thread, not per row).
@@ -1483,19 +1718,41 @@ __global__ __launch_bounds__(256) void fp8_amax(AssembleArgs a) {
   const int items = (row1 - row0) * per_row;
   const RingMap rm = ring_map(L, s, r);
   uint32_t mk = 0, mv = 0;
-  for (int it = tid(); it < items; it += nthreads()) {
-    const int row = row0 + it / per_row, piece = it % per_row;
-    const int t = row_source(row, L, s, r, keff, sg, rm);
-    if (t < 0) continue;
-    const u32x4 x = piece < kp ? *((const u32x4*)((const uint16_t*)a.k + (in_row0 + t) * a.dk) + piece)
-                               : *((const u32x4*)((const uint16_t*)a.v + (in_row0 + t) * a.dv) + (piece - kp));
-    uint32_t m = 0;
+  // as in assemble: kAsmU pieces a thread, all their reads in flight together
+  const int step_r = nthreads() / per_row, step_p = nthreads() % per_row;
+  int cur_r = tid() / per_row, cur_p = tid() % per_row;
+  for (int it0 = tid(); it0 < items; it0 += kAsmU * nthreads()) {
+    int piece_u[kAsmU], src_t[kAsmU];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) m = max(m, max(x[i] & 0x7fffu, (x[i] >> 16) & 0x7fffu));
-    if (piece < kp)
-      mk = max(mk, m);
-    else
-      mv = max(mv, m);
+    for (int u = 0; u < kAsmU; ++u) {
+      piece_u[u] = cur_p;
+      src_t[u] = it0 + u * nthreads() < items ? row_source(row0 + cur_r, L, s, r, keff, sg, rm) : -1;
+      cur_r += step_r;
+      cur_p += step_p;
+      if (cur_p >= per_row) {
+        cur_p -= per_row;
+        ++cur_r;
+      }
+    }
+    u32x4 x[kAsmU];
+#pragma unroll
+    for (int u = 0; u < kAsmU; ++u) {
+      const int piece = piece_u[u], t = src_t[u];
+      x[u] = u32x4{0u, 0u, 0u, 0u};
+      if (t >= 0)
+        x[u] = piece < kp ? *((const u32x4*)((const uint16_t*)a.k + (in_row0 + t) * a.dk) + piece)
+                          : *((const u32x4*)((const uint16_t*)a.v + (in_row0 + t) * a.dv) + (piece - kp));
+    }
+#pragma unroll
+    for (int u = 0; u < kAsmU; ++u) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m = max(m, max(x[u][i] & 0x7fffu, (x[u][i] >> 16) & 0x7fffu));
+      if (piece_u[u] < kp)
+        mk = max(mk, m);
+      else
+        mv = max(mv, m);
+    }
   }
   mk = block_max_u32(mk, lds);
   mv = block_max_u32(mv, lds);
@@ -1507,7 +1764,6 @@ __global__ __launch_bounds__(256) void fp8_amax(AssembleArgs a) {
 // head); threads walk (row, 8-element piece) pairs so every lane copies, kAsmU
 // pairs at a time: their selected-index reads, then their row reads, are all
 // issued before the first store (two memory round trips per kAsmU pieces).
-constexpr int kAsmU = 8;
 template <typename In, typename Out>
 __global__ __launch_bounds__(256) void assemble(AssembleArgs a) {
   const int bg = bid_y(), b = bg / a.Hkv, g = bg % a.Hkv;
@@ -1668,7 +1924,11 @@ Geometry compress_geometry(const snap_params& p, int n_seq, int max_len) {
   g.off_P = off;
   off = align256(off + (size_t)groups * max_len * sizeof(float));
   g.off_hist = off;
-  off = align256(off + (size_t)3 * groups * kRadixBins * sizeof(uint32_t));
+  off = align256(off + (size_t)groups * (kHistBins + kSubBins) * sizeof(uint32_t));
+  g.off_list = off;
+  off = align256(off + (size_t)groups * kListCap * sizeof(uint2));
+  g.off_list_n = off;
+  off = align256(off + (size_t)groups * sizeof(int32_t));
   g.off_state = off;
   off = align256(off + (size_t)groups * sizeof(RadixState));
   g.off_counts = off;
@@ -1813,6 +2073,8 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     ra.band_n = band_n;
     ra.lengths = lengths;
     ra.hist = hist;
+    ra.list_n = (int32_t*)(w + geo.off_list_n);
+    ra.reset_wgs = (geo.rows_pad + kReduceRows - 1) / kReduceRows;
     ra.state = state;
     ra.groups = groups;
     ra.Hkv = p.n_kv_heads;
@@ -1822,8 +2084,7 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     ra.topk = p.topk;
     ra.rows_pad = geo.rows_pad;
     ra.n_kchunks = stats_given ? 1 : geo.n_kchunks;
-    hipLaunchKernelGGL(stats_reduce, dim3((geo.rows_pad + kReduceRows - 1) / kReduceRows, groups), dim3(256), 0,
-                       stream, ra);
+    hipLaunchKernelGGL(stats_reduce, dim3(ra.reset_wgs, groups), dim3(256), 0, stream, ra);
     if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
 
     sa.key_chunk = geo.col_chunk;
@@ -1838,6 +2099,14 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     se.pooled_out = pooled_out;
     se.lengths = lengths;
     se.hist = hist;
+    se.list = (uint2*)(w + geo.off_list);
+    se.list_n = (int32_t*)(w + geo.off_list_n);
+    {
+      const float most = (float)geo.rows;
+      uint32_t bits;
+      memcpy(&bits, &most, sizeof(bits));
+      se.hist_top = bits >> 17;
+    }
     se.state = state;
     se.counts = counts;
     se.sel = sel;
@@ -1854,13 +2123,10 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     se.pool = p.pool;
     se.n_splits = geo.n_splits;
     dim3 sgrid(geo.n_splits, groups);
-    hipLaunchKernelGGL(pool_hist0, sgrid, dim3(kSelThreads), 0, stream, se);
-    hipLaunchKernelGGL(radix_scan, dim3(groups), dim3(kSelThreads), 0, stream, se, 0);
-    hipLaunchKernelGGL(radix_pass, sgrid, dim3(kSelThreads), 0, stream, se, 1);
-    hipLaunchKernelGGL(radix_scan, dim3(groups), dim3(kSelThreads), 0, stream, se, 1);
-    hipLaunchKernelGGL(radix_pass, sgrid, dim3(kSelThreads), 0, stream, se, 2);
-    hipLaunchKernelGGL(radix_scan, dim3(groups), dim3(kSelThreads), 0, stream, se, 2);
-    hipLaunchKernelGGL(select_count, sgrid, dim3(kSelThreads), 0, stream, se);
+    hipLaunchKernelGGL(pool_hist, sgrid, dim3(kSelThreads), 0, stream, se);
+    hipLaunchKernelGGL(select_refine, sgrid, dim3(kSelThreads), 0, stream, se);
+    hipLaunchKernelGGL(select_collect, sgrid, dim3(kSelThreads), 0, stream, se);
+    hipLaunchKernelGGL(select_threshold, dim3(groups), dim3(kThrThreads), 0, stream, se);
     // fp64 re-score of the candidates next to the threshold, then the final
     // decision among them
     BandArgs ba;
@@ -1892,12 +2158,16 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     ba.rows_pad = geo.rows_pad;
     ba.n_splits = geo.n_splits;
     ba.in_f32 = !bf;
-    ba.band_wgs = kBandWGs;
+    // workgroups per group of band_rescore, its work items strided over them:
+    // 576-wide keys (four row passes of long rows per key block) take about 1024
+    // in all (16 groups: 45 us with 16 each, 34 with 64); narrower ones 16, where
+    // more only repeat the sorting of the members (8 groups: 10.8 us, 12.9 with 64)
+    ba.band_wgs = p.d_qk <= 128 || groups >= 64 ? 16 : (groups <= 16 ? 64 : 1024 / groups);
     // query-dim slices per score row: 8 for 576-wide bf16 rows and for fp32
     // rows, else 4 (as band_rescore dispatches)
     ba.rows_per_pass = kBandThreads / ((!bf || p.d_qk == 576) ? 8 : 4);
     ba.scale2 = (double)scale * 1.4426950408889634074;
-    hipLaunchKernelGGL(band_rescore, dim3(kBandWGs, groups), dim3(kBandThreads), 0, stream, ba);
+    hipLaunchKernelGGL(band_rescore, dim3(ba.band_wgs, groups), dim3(kBandThreads), 0, stream, ba);
     hipLaunchKernelGGL(band_decide, dim3(groups), dim3(kSelThreads), 0, stream, ba);
     hipLaunchKernelGGL(select_write, sgrid, dim3(kSelThreads), 0, stream, se);
     if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;

@@ -175,7 +175,7 @@ struct Geometry {
   int n_colchunks;
   int n_splits;     // candidate splits per group in pool/select
   int n_rowblocks;   // assemble row blocks per group
-  size_t off_stats, off_rowref, off_A, off_P, off_hist, off_state, off_counts, off_sel, off_amax;
+  size_t off_stats, off_rowref, off_A, off_P, off_hist, off_list, off_list_n, off_state, off_counts, off_sel, off_amax;
   // fp64 re-score of the candidates next to the selection threshold
   size_t off_rowz, off_band_n, off_band_idx, off_band_p, off_band_above, off_A64;
   size_t compress_bytes;
@@ -193,19 +193,25 @@ struct Geometry {
 constexpr int kKeyTile = 64;      // key chunks of the score passes are multiples of this
 constexpr int kCandChunk = 2048;  // candidates per pool/select workgroup
 constexpr int kSelThreads = 256;
-constexpr int kRadixBins = 2048;
+constexpr int kHistBins = 4096;  // bins of the pooled scores' leading bits
+constexpr int kSubBits = 11;     // parts of the bin that holds the threshold
+constexpr int kSubBins = 1 << kSubBits;
+// Candidates next to the threshold that a group's list holds (a few tens,
+// unless many scores are equal).
+constexpr int kListCap = 2048;
 // Candidates whose pooled score lies within a factor 1 +- 2^-17 of the K-th
 // largest are re-scored in fp64 before the final selection, up to this many
 // per (sequence, KV head); a group with more keeps its fp32 selection.
 constexpr int kBandCap = 512;
 
 struct RadixState {
-  uint32_t prefix;  // decided high bits of the threshold
-  uint32_t mask;    // which bits are decided
-  int32_t krem;     // how many elements equal to the threshold prefix still to take
+  uint32_t prefix;  // the threshold's bits
+  int32_t bin;      // histogram bin that holds it
+  int32_t krem;     // how many elements equal to the threshold to take
   int32_t keff;     // how many candidates are kept in total
-  int32_t mode;     // 0: nothing kept, 1: all candidates kept, 2: radix select
-  int32_t pad[3];
+  int32_t mode;     // 0: nothing kept, 1: all candidates kept, 2: by threshold
+  int32_t sub;      // part of that bin
+  int32_t pad[2];
 };
 
 // scale * log2(e) split as hi + lo (hi: fp32 rounded toward zero; lo > 0)
