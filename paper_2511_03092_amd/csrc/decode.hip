@@ -1470,7 +1470,12 @@ snap_status launch_decode(const snap_params& p, const snap_cache& c, const int32
     hipLaunchKernelGGL(k, grid, dim3(64), 0, stream, a);
   } else {
     dim3 grid(geo.n_chunks, n * p.n_q_heads);
-    hipLaunchKernelGGL((decode_generic<float>), grid, dim3(64), 0, stream, a);
+    if (p.kv_dtype == SNAP_F32)
+      hipLaunchKernelGGL((decode_generic<float>), grid, dim3(64), 0, stream, a);
+    else if (p.kv_dtype == SNAP_BF16)
+      hipLaunchKernelGGL((decode_generic<uint16_t>), grid, dim3(64), 0, stream, a);
+    else
+      hipLaunchKernelGGL((decode_generic<uint8_t>), grid, dim3(64), 0, stream, a);
   }
   if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
   CombineArgs ca;

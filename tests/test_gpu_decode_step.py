@@ -119,6 +119,17 @@ def test_step_latent_fp8_new_row_is_the_last(lengths):
     run_case(wl, p, lengths, [1, 0], 2, 4, torch.float32, TOL["fp8"], fp8_scales=True, fused="alt")
 
 
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_step_latent_of_two_kv_heads(kv):
+    """576-wide latent rows of more than one KV head (decode_generic)."""
+    wl = synth.small(synth.WORKLOADS["mla-8head-61layer-b16-128k"], n_kv_heads=2, recent=64, topk=300, obs_window=8,
+                     kv_dtype=kv)
+    p = params_of(wl)
+    lengths = [900, 211]
+    _announce(f"decode_step {kv} latent, 2 KV heads: lengths {lengths}")
+    run_case(wl, p, lengths, [1, 0], 2, 6, torch.float32, TOL[kv], fp8_scales=kv == "fp8", fused="alt")
+
+
 def test_step_fp8_fused_and_fp32_two_launch_paths():
     wl = synth.small(GQA, kv_dtype="fp8")
     p = params_of(wl)
