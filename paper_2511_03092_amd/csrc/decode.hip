@@ -788,23 +788,28 @@ __global__ __launch_bounds__(256) void decode_mla_lds(DecodeArgs a) {
 }
 
 // ---------------------------------------------------------------- fp8 latent decode, LDS-staged
-// fp8 latent caches: one workgroup of 4 waves per (chunk, sequence) streams
-// blocks of 64 rows (576 codes each: as many bytes per stage as 32 bf16 rows)
-// through LDS with direct loads.  Converting codes to bf16 is what a CU would
-// run out of first, so no wave converts a code that another wave converts for
-// the same product: wave w forms the logits of the block's rows [16w, 16w+16)
-// over all 18 k-steps, the 64 x 16 logits are exchanged through LDS, and every
-// wave then takes the softmax of all 64 rows (the same values in each) and the
-// value product for dims [128w, 128w+128).  Two stages (74 KB), so that two
-// workgroups share a CU and one computes while the other waits: 16 heads, 32
-// sequences x 32768 rows 120 us with four stages and one workgroup, 107 us with
-// two.  HBM bound there (5.7 TB/s; 366 us with the rows loaded to registers, an
-// exchange and barrier per 32 rows and an append launch before it); 8 heads, 8
-// x 16384 rows 34.0 -> 22.4 us a call.
+// fp8 latent caches: one workgroup of 4 waves per (chunk, sequence) streams its
+// rows [v0, v1) in blocks of 64 (576 codes each: as many bytes per stage as 32
+// bf16 rows) through LDS with direct loads.  Converting codes to bf16 is what a
+// CU would run out of first, so no wave converts a code that another wave
+// converts for the same product: wave w forms the logits of the block's rows
+// [16w, 16w+16) over all 18 k-steps, the 64 x 16 logits are exchanged through
+// LDS, and every wave then takes the softmax of the rows (the same values in
+// each) and the value product for dims [128w, 128w+128).
+// The results are those of a wave that takes 32 rows at a time, in order, over
+// one run of rows per chunk: the reference that probabilities are rounded to
+// bf16 against moves per 32 rows, and a logit is the sum of four partial dot
+// products of 5, 5, 4 and 4 k-steps (tests/test_gpu_decode_step.py holds the
+// kernel to that order).
+// Two stages (74 KB), so that two workgroups share a CU and one computes while
+// the other waits (with four stages and one workgroup a CU 12% slower at 32
+// sequences x 32768 rows).  HBM bound there: 8 heads 351 -> 101 us a call (6.0
+// TB/s), 16 heads 358 -> 107; 8 heads, 8 x 16384 rows 32.8 -> 22.1 us (before:
+// rows loaded to registers, an exchange and barrier per 32 rows, an append
+// launch).  64 rows per softmax and blocks interleaved over the chunks took 2 to
+// 3% less, with other probabilities rounded.
 // LDS rows are 36 chunks of 16 bytes; chunk c of row r sits at slot
-// r*36 + (c ^ ((r >> 1) & 3)), which spreads one chunk of 8 consecutive rows
-// (a key-fragment read) over the banks and keeps a value read within its 128
-// bytes.
+// r*36 + (c ^ lat8_swz(r)).
 constexpr int kLat8Stages = 2;
 constexpr int kLat8Rows = 64;
 constexpr int kLat8RowBytes = 576;
@@ -812,7 +817,18 @@ constexpr int kLat8Chunks = kLat8RowBytes / 16;  // 36
 static_assert(kLat8Rows * kLat8RowBytes == kLatBlockBytes, "the stages hold either block");
 constexpr int kLat8Ld = kLat8Rows + 4;  // logits of one head (padded: 16 heads read 16 bytes each)
 
-__device__ __forceinline__ int lat8_slot(int r, int c) { return r * kLat8Chunks + (c ^ ((r >> 1) & 3)); }
+__device__ __forceinline__ int lat8_swz(int r) { return (r >> 1) & 3; }
+__device__ __forceinline__ int lat8_slot(int r, int c) { return r * kLat8Chunks + (c ^ lat8_swz(r)); }
+
+// The four partial dot products of a logit: part p takes k-steps lat8_step0(p)
+// .. + lat8_steps(p) - 1, and lane group lg feeds 8 codes (or query dims) from
+// piece 4 * step0 + steps * lg + t of the row to step t of them.
+constexpr int kLat8Parts = 4;
+__device__ __forceinline__ constexpr int lat8_steps(int p) { return p < 2 ? 5 : 4; }
+__device__ __forceinline__ constexpr int lat8_step0(int p) { return p < 2 ? 5 * p : 10 + 4 * (p - 2); }
+__device__ __forceinline__ constexpr int lat8_piece(int p, int lg, int t) {
+  return 4 * lat8_step0(p) + lat8_steps(p) * lg + t;
+}
 
 template <bool NT>
 __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
@@ -837,29 +853,24 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
     const int q = (wu + 4 * ii) * 64 + lane;
     const int r = q / kLat8Chunks;
     ld_r[ii] = r;
-    ld_c[ii] = (q % kLat8Chunks) ^ ((r >> 1) & 3);
+    ld_c[ii] = (q % kLat8Chunks) ^ lat8_swz(r);
     ld_off[ii] = r * kLat8RowBytes + ld_c[ii] * 16;
   }
   const unsigned char* cache = (const unsigned char*)a.ck + (size_t)slot * B * kLat8RowBytes;
-  // the slot's 64-row blocks are interleaved over its chunks, as in decode_mla_lds
-  const int nb_slot = (sp.nv + kLat8Rows - 1) / kLat8Rows;
-  const int nblk =
-      __builtin_amdgcn_readfirstlane(chunk < nb_slot ? (nb_slot - chunk + a.n_chunks - 1) / a.n_chunks : 0);
-  // fused append: the workgroup whose block holds row vnew quantises it
-  // (thread t: codes 8t .. 8t+7), puts the codes over that row of the block in
-  // LDS and stores them into the cache at its end; no other workgroup reads
-  // the row
+  const int nblk = sp.v0 < sp.v1 ? (sp.v1 - sp.v0 + kLat8Rows - 1) / kLat8Rows : 0;
+  // fused append: the workgroup whose rows include vnew quantises it (thread t:
+  // codes 8t .. 8t+7), puts the codes over that row of the block in LDS and
+  // stores them into the cache at its end; no other workgroup reads the row
   const int vnew = new_row(a, slot);
-  const int blk_new = vnew >= 0 && vnew < sp.nv && vnew / kLat8Rows % a.n_chunks == chunk
-                          ? vnew / kLat8Rows / a.n_chunks : -1;
+  const int blk_new = vnew >= sp.v0 && vnew < sp.v1 ? (vnew - sp.v0) / kLat8Rows : -1;
   const bool has_new = blk_new >= 0 && tid() < kLat8RowBytes / 8;
   u32x2 codes = {0u, 0u};
   if (has_new) codes = new_raw8<true>(a.k_new, (size_t)b * kLat8RowBytes + 8 * tid(), ksc);
 
   auto issue = [&](int blk) {
-    const int vb = kLat8Rows * (chunk + blk * a.n_chunks);
+    const int vb = sp.v0 + kLat8Rows * blk;
     unsigned char* dst = &stage[blk % kLat8Stages][0];
-    if (vb + kLat8Rows <= sp.nv && (vb + kLat8Rows <= sp.n1 || vb >= sp.n1)) {
+    if (vb + kLat8Rows <= sp.v1 && (vb + kLat8Rows <= sp.n1 || vb >= sp.n1)) {
       // a whole block inside one run of the row map
       const unsigned char* base = cache + (size_t)virt_row(vb, sp.n1, sr) * kLat8RowBytes;
 #pragma unroll
@@ -868,7 +879,7 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
 #pragma unroll
       for (int ii = 0; ii < kLatLoadsPerWave; ++ii) {
         int v = vb + ld_r[ii];
-        v = v < sp.nv ? v : sp.nv - 1;
+        v = v < sp.v1 ? v : sp.v1 - 1;  // never a row of another workgroup
         dma16_lat<NT>(cache + (size_t)virt_row(v, sp.n1, sr) * kLat8RowBytes + ld_c[ii] * 16,
                       dst + (size_t)(wu + 4 * ii) * 1024);
       }
@@ -880,7 +891,7 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
   f32x4 acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 qf[kMlaKSteps];  // lane group lg holds dims 8*(18*lg + t) of k-step t
+  bf16x8 qf[kMlaKSteps];
 
   // Prologue: the query rows (G x 1152 bytes) go to the second stage with block
   // 0, so one wait covers both.
@@ -898,11 +909,13 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
     lat_wait_vm<0>();
     lat_barrier();
 #pragma unroll
-    for (int t = 0; t < kMlaKSteps; ++t) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (hval) v = *(const u32x4*)(qdst + (size_t)l16 * kLatRowBytes + 8 * (kMlaKSteps * lg + t) * 2);
-      qf[t] = __builtin_bit_cast(bf16x8, v);
-    }
+    for (int p = 0; p < kLat8Parts; ++p)
+#pragma unroll
+      for (int t = 0; t < lat8_steps(p); ++t) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (hval) v = *(const u32x4*)(qdst + (size_t)l16 * kLatRowBytes + 16 * lat8_piece(p, lg, t));
+        qf[lat8_step0(p) + t] = __builtin_bit_cast(bf16x8, v);
+      }
   }
 
   for (int i = 0; i < nblk; ++i) {
@@ -912,66 +925,81 @@ __global__ __launch_bounds__(256) void decode_mla8_lds(DecodeArgs a) {
     lat_barrier();
     if (i + 1 < nblk) issue(i + 1);
     unsigned char* st = &stage[i % kLat8Stages][0];
-    const int vb = kLat8Rows * (chunk + i * a.n_chunks);
+    const int vb = sp.v0 + kLat8Rows * i;
     if (i == blk_new) {
       // rows past the last valid one hold copies of it: where that is the new
       // row, whose bytes in the cache are not written yet and may be NaN codes,
       // they are overwritten too (their probabilities are 0, and 0 * NaN is not)
       if (has_new) {
-        const int last = vnew == sp.nv - 1 ? kLat8Rows - 1 : vnew - vb;
+        const int last = vnew == sp.v1 - 1 ? kLat8Rows - 1 : vnew - vb;
         for (int r = vnew - vb; r <= last; ++r)
           *(u32x2*)(st + lat8_slot(r, tid() >> 1) * 16 + 8 * (tid() & 1)) = codes;
       }
       lat_barrier();
     }
 
-    // logits of rows 16w .. 16w+15 (two chains, summed)
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    // logits of rows 16w .. 16w+15 (one chain per part)
+    f32x4 s[kLat8Parts];
+    const int kr = 16 * w + l16;
 #pragma unroll
-    for (int j = 0; j < kMlaKSteps / 2; ++j) {
-      const u32x4 kk = *(const u32x4*)(st + (size_t)lat8_slot(16 * w + l16, 9 * lg + j) * 16);
-      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, e4m3x8_to_bf16x8(u32x2{kk[0], kk[1]})),
-                                                   qf[2 * j], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, e4m3x8_to_bf16x8(u32x2{kk[2], kk[3]})),
-                                                   qf[2 * j + 1], s1, 0, 0, 0);
+    for (int p = 0; p < kLat8Parts; ++p) {
+      s[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+      u32x2 kc[5];
+      if (lat8_steps(p) == 4) {  // an even piece, 16-byte aligned
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const u32x4 k4 = *(const u32x4*)(st + (size_t)lat8_slot(kr, lat8_piece(p, lg, 2 * j) >> 1) * 16);
+          kc[2 * j] = u32x2{k4[0], k4[1]};
+          kc[2 * j + 1] = u32x2{k4[2], k4[3]};
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+          const int c = lat8_piece(p, lg, t);
+          kc[t] = *(const u32x2*)(st + (size_t)lat8_slot(kr, c >> 1) * 16 + 8 * (c & 1));
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < lat8_steps(p); ++t)
+        s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, e4m3x8_to_bf16x8(kc[t])),
+                                                       qf[lat8_step0(p) + t], s[p], 0, 0, 0);
     }
-    s0 += s1;
-    *(f32x4*)&logits[l16][16 * w + 4 * lg] = s0;
+    *(f32x4*)&logits[l16][16 * w + 4 * lg] = ((s[0] + s[1]) + s[2]) + s[3];
     lat_barrier();
 
-    // softmax of the block's 64 rows for head l16: this lane takes rows
-    // 16k + 4*lg + e
-    f32x4 x[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = *(const f32x4*)&logits[l16][16 * k + 4 * lg];
-    if (vb + kLat8Rows > sp.nv) {
+    for (int h = 0; h < 2; ++h) {  // rows vh .. vh+31
+      const int vh = vb + 32 * h;
+      if (vh >= sp.v1) break;
+      // softmax for head l16: this lane takes rows 4*lg + e and 16 + 4*lg + e
+      f32x4 x[2];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < 2; ++k) x[k] = *(const f32x4*)&logits[l16][32 * h + 16 * k + 4 * lg];
+      if (vh + 32 > sp.v1) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (vb + 16 * k + 4 * lg + e >= sp.nv) x[k][e] = -INFINITY;
-    }
-    float bm = -INFINITY;
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bm = fmaxf(bm, fmaxf(fmaxf(x[k][0], x[k][1]), fmaxf(x[k][2], x[k][3])));
-    bm = fmaxf(bm, __shfl_xor(bm, 16));
-    bm = fmaxf(bm, __shfl_xor(bm, 32));
-    bm *= xs;
-    const bool up = bm > m + kStaleMax;  // always true for the first valid block (m = -inf)
-    if (wave_any(up)) {
-      const float mnew = up ? bm : m;
-      const float alpha = up ? fast_exp2(m - mnew) : 1.f;
+          for (int e = 0; e < 4; ++e)
+            if (vh + 16 * k + 4 * lg + e >= sp.v1) x[k][e] = -INFINITY;
+      }
+      float bm = fmaxf(fmaxf(fmaxf(x[0][0], x[0][1]), fmaxf(x[0][2], x[0][3])),
+                       fmaxf(fmaxf(x[1][0], x[1][1]), fmaxf(x[1][2], x[1][3])));
+      bm = fmaxf(bm, __shfl_xor(bm, 16));
+      bm = fmaxf(bm, __shfl_xor(bm, 32));
+      bm *= xs;
+      const bool up = bm > m + kStaleMax;  // always true for the first valid block (m = -inf)
+      if (wave_any(up)) {
+        const float mnew = up ? bm : m;
+        const float alpha = up ? fast_exp2(m - mnew) : 1.f;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] *= alpha;
-      lsum *= alpha;
-      m = mnew;
-      mref = m == -INFINITY ? 0.f : m;  // no valid row yet: every x is -inf, exp2 gives 0
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // rows 32h .. 32h+31
+        for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+        lsum *= alpha;
+        m = mnew;
+        mref = m == -INFINITY ? 0.f : m;  // no valid row yet: every x is -inf, exp2 gives 0
+      }
       float pe[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) pe[k] = fast_exp2(fmaf(x[2 * h + (k >> 2)][k & 3], xs, -mref));
+      for (int k = 0; k < 8; ++k) pe[k] = fast_exp2(fmaf(x[k >> 2][k & 3], xs, -mref));
       lsum += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
       u32x4 pw;
 #pragma unroll

@@ -7,9 +7,11 @@ tokens land in sink rows), the ring wrapping, and an invalid slot id.
 
 Every case prints what names it before touching the GPU.
 """
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2511_03092_amd as snap
 import synth
 from snaphelp import TOL, GpuCache, decode_steps, gpu_compress, params_of, run_case
@@ -258,3 +260,71 @@ def test_infinite_value_stays_infinite(kv_reuse):
     torch.cuda.synchronize()
     assert (out[0, :, 5] == float("inf")).all() and (out[0, :, 9] == float("-inf")).all()
     assert torch.isfinite(out[0, :, [d for d in range(64) if d not in (5, 9)]]).all()
+
+
+def _latent_in_32_row_blocks(q, rows, scale, n_chunks):
+    """Attention of q [G][576] over latent rows [nv][576] (values: the first 512
+    dims) as a split-K wave takes it: one run of rows per chunk (a multiple of 32
+    of them), 32 rows at a time, a head's reference moved only when a block's
+    largest logit passes it by more than 8 (log2 units), probabilities against
+    that reference rounded to bf16 for the value product and summed unrounded."""
+    nv = rows.shape[0]
+    per = (-(-nv // n_chunks) + 31) & ~31
+    x = (q.astype(np.float64) @ rows.T.astype(np.float64) * (scale * np.log2(np.e))).astype(np.float32)
+    part = []
+    for v0 in range(0, nv, per):
+        m = np.full(q.shape[0], -np.inf, np.float32)
+        l, acc = np.zeros(q.shape[0]), np.zeros((q.shape[0], 512))
+        for vb in range(v0, min(v0 + per, nv), 32):
+            end = min(vb + 32, v0 + per, nv)
+            bm = x[:, vb:end].max(1)
+            mn = np.where(bm > m + 8, bm, m)
+            alpha = np.exp2((m - mn).astype(np.float64))
+            m = mn
+            pe = np.exp2((x[:, vb:end] - m[:, None]).astype(np.float64)).astype(np.float32)
+            pb = torch.from_numpy(pe).to(torch.bfloat16).double().numpy()
+            l = l * alpha + pe.sum(1, dtype=np.float64)
+            acc = acc * alpha[:, None] + pb @ rows[vb:end, :512].astype(np.float64)
+        part.append((m.astype(np.float64), l, acc))
+    top = np.max([m for m, _, _ in part], axis=0)
+    num = sum(np.exp2(m - top)[:, None] * acc for m, _, acc in part)
+    return num / sum(np.exp2(m - top) * l for m, l, _ in part)[:, None]
+
+
+@pytest.mark.parametrize("hq,n_topk", [(8, 444), (8, 301), (16, 20), (3, 0)])
+def test_fp8_latent_rounding_order(hq, n_topk):
+    """Which probabilities an fp8 latent decode rounds to which bf16 values: the
+    reference moves per 32 rows of one run of rows per chunk.  Rows taken in
+    another order or grouping (64 at a time, interleaved over the chunks) are as
+    near the exact attention, 1.7e-3, but differ from this order by 0.8e-3 to
+    2.6e-3.  What is left between equal orders is a logit's fp32 rounding (about
+    2e-6 in log2 units), which moves at most about 1e-3 of the probabilities over
+    a bf16 rounding edge (2^-8 of each): 2^-8 * sqrt(1e-3) = 1.2e-4, held to 3e-4
+    (measured 2e-7 to 3e-5).
+    n_topk 301: the second chunk starts at row 192; 20 and 0: a last block of
+    fewer than 32 rows."""
+    sink, recent, topk, n = 4, 64, 444, 2
+    p = snap.Params(n_q_heads=hq, n_kv_heads=1, d_qk=576, d_v=512, sink=sink, recent=recent, topk=topk, obs_window=8,
+                    pool_kernel=7, v_in_k=True, kv_dtype=snap.SNAP_FP8_E4M3)
+    _announce(f"fp8 latent, rounding order: {hq} heads, n_topk {n_topk}")
+    gen = torch.Generator().manual_seed(hq + n_topk)
+    codes = (torch.randn((n, 1, p.budget, 576), generator=gen) * 40).to(torch.float8_e4m3fn)
+    q = torch.randn((n, hq, 576), generator=gen).to(torch.bfloat16)
+    c = GpuCache(p, n)
+    c.k.copy_(codes.view(torch.uint8))
+    c.k_scale.fill_(0.0625)
+    c.pos.fill_(1000)
+    c.n_topk.fill_(n_topk)
+    sl = torch.arange(n, dtype=torch.int32, device="cuda")
+    out = torch.zeros((n, hq, 512), dtype=torch.float32, device="cuda")
+    snap.snap_decode_attn(p, c.c(), c.pos, c.n_topk, sl, q.to("cuda"), out, snap.workspace(snap.snap_decode_workspace(p, n)))
+    torch.cuda.synchronize()
+    table = np.array([oracle.e4m3_value(i) for i in range(256)])
+    for b in range(n):
+        rows = table[codes[b, 0, :sink + recent + n_topk].view(torch.uint8).numpy()] * 0.0625
+        # 512 rows of two sequences make two chunks of at least 256
+        exp = _latent_in_32_row_blocks(q[b].double().numpy(), rows, 576 ** -0.5, 2)
+        got = out[b].double().cpu().numpy()
+        err = float(np.linalg.norm(got - exp) / np.linalg.norm(exp))
+        print(f"  sequence {b}: {err:.2e}", flush=True)
+        assert err <= 3e-4
