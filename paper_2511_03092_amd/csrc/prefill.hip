@@ -22,13 +22,12 @@
 #include <math.h>
 
 #include "lds_dma.h"
+#include "prefill_order.h"
 #include "snap_internal.h"
 
 namespace snap {
 
 constexpr int kPfTK = 64;  // keys per tile
-constexpr long kPfSmallBlocks = 1024;
-constexpr size_t kPfSpreadBytes = (size_t)64 << 20;
 
 struct PrefillArgs {
   const uint16_t* q;   // [n_seq][Hq][max_len][D]
@@ -39,17 +38,10 @@ struct PrefillArgs {
   float2* stats;       // [n_seq*Hkv][rows_pad]: (max, sum of 2^(y - max)), y in log2 units
   uint16_t* qobs;      // [n_seq][Hq][w][D]
   int Hq, Hkv, G, max_len, ld_vt, w, sink, recent, norm, rows, rows_pad, want_stats;
-  int P;               // query positions per workgroup
-  int n_qblocks, groups;  // workgroups per group (max_len / P rounded up), n_seq * Hkv
-  int whole, turn;        // groups that keep to one XCD; blocks of a position after which the others' XCDs move on
+  PrefillOrder order;  // (prefill_order.h)
   float scale2;        // softmax scale * log2(e) as scale2 + scale2_lo (split_scale2)
   float scale2_lo;
 };
-
-// Query positions per workgroup of nw waves (32 query rows each) for G heads per
-// KV head: the rows of a workgroup are (head, position) pairs of one KV head, so
-// every key tile in LDS serves all G heads.
-static inline int prefill_positions(int nw, int G) { return 32 * nw / G; }
 
 // Head within the group and position offset within the workgroup of row block
 // rb (16 rows) of wave w: the workgroup's row blocks run over the G heads
@@ -136,27 +128,12 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attn(PrefillArgs a) {
 
   const int lane = tid() & 63, wave = tid() >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
-  // Workgroup order: consecutive workgroups go to the 8 XCDs in turn.  Of the
-  // first `whole` KV heads (groups), a multiple of 8, XCD x takes x, x+8, x+16,
-  // ... one after the other, each from its last positions (the most keys) to its
-  // first, so that the workgroups resident on one XCD share the same K and V
-  // tiles in its L2.  The blocks of the `mixed` other groups go round all XCDs,
-  // each group's by turns to each XCD.
   int bg, kblk;
-  const int nw = a.whole * a.n_qblocks;
-  if (bid_x() < nw) {
-    const int xcd = bid_x() % 8, r = bid_x() / 8;
-    bg = (r / a.n_qblocks) * 8 + xcd;
-    kblk = r % a.n_qblocks;
-  } else {
-    const int i = bid_x() - nw, mixed = a.groups - a.whole;
-    kblk = i / mixed;
-    bg = a.whole + (i % mixed + kblk / a.turn) % mixed;
-  }
+  prefill_block(a.order, bid_x(), bg, kblk);
   const int b = bg / a.Hkv, g = bg % a.Hkv;
   int L = uniform(a.lengths[b]);
   L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
-  const int P = a.P;
+  const int P = a.order.P;
   const int top = L - P * kblk;  // one past this workgroup's last position
   if (top <= 0) return;
   if (!debug_check(top <= L && L <= a.max_len, kDbgPrefill)) return;
@@ -455,40 +432,15 @@ snap_status launch_prefill_attn(const snap_params& p, int n_seq, const int32_t* 
   pa.rows = geo.rows;
   pa.rows_pad = geo.rows_pad;
   pa.want_stats = want_stats ? 1 : 0;
-  // Waves per workgroup.  128-wide: 8 (every tile load serves 256 rows), but 4
-  // for a call of few workgroups, whose time is that of its longest one, 64 keys
-  // a turn: up to 1024 of them (one 2048-token prompt, 32 heads, 128 of them:
-  // 109 -> 84 us; 8192 tokens, 512: 656 -> 644; 16384 tokens, 2048: 2187 with
-  // 8, 2229 with 4).  64-wide: 4, three workgroups per CU at 155 registers
-  // against one of 8 waves (8 ragged prompts of up to 3000 tokens, 288 -> 187
-  // us; 4 of up to 16384, 2377 -> 2088).  More than 8 heads a group need 8
-  // waves for a block of 16 positions each.
-  const long blocks8 = (long)groups * ((max_len + prefill_positions(8, G) - 1) / prefill_positions(8, G));
-  const int nw = G <= 8 && (p.d_qk == 64 || blocks8 <= kPfSmallBlocks) ? 4 : 8;
-  pa.P = prefill_positions(nw, G);
+  pa.order = prefill_order(n_seq, p.n_kv_heads, G, p.d_qk, max_len);
+  const int nw = pa.order.waves;
   split_scale2(scale, pa.scale2, pa.scale2_lo);
-  pa.n_qblocks = (max_len + pa.P - 1) / pa.P;
-  pa.groups = groups;
-  // Groups that do not fill the 8 XCDs evenly are spread over all of them: one
-  // KV head of 16384 tokens kept one XCD of eight busy (7.32 ms, now 1.13).  So
-  // are all groups of a batch whose sequences' heads are not a multiple of 8 (its
-  // XCDs would hold different sequences, and wait for the longest), while K and V
-  // together are small enough that each XCD reading them costs little: four
-  // ragged prompts of up to 16384 tokens with two 128-wide KV heads, 64 MB, 2544
-  // -> 1846 us; with four 64-wide ones, 2354 -> 2380.
-  const size_t kv_bytes = (size_t)groups * max_len * p.d_qk * 4;
-  const bool spread = n_seq > 1 && p.n_kv_heads % 8 != 0 && kv_bytes <= kPfSpreadBytes;
-  pa.whole = spread ? 0 : groups / 8 * 8;
-  const int mixed = groups - pa.whole;
-  // i % 8 and i % mixed repeat together every 8 / gcd(mixed, 8) positions
-  pa.turn = mixed % 8 == 0 ? 1 : (mixed % 4 == 0 ? 2 : (mixed % 2 == 0 ? 4 : 8));
-  dim3 grid(groups * pa.n_qblocks);
   void (*kern)(PrefillArgs);
   if (p.d_qk == 128)
     kern = nw == 8 ? prefill_attn<4, 8> : prefill_attn<4, 4>;
   else
     kern = nw == 8 ? prefill_attn<2, 8> : prefill_attn<2, 4>;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, stream, pa);
+  hipLaunchKernelGGL(kern, dim3(pa.order.grid), dim3(64 * nw), 0, stream, pa);
   if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
   return SNAP_OK;
 }

@@ -1,0 +1,92 @@
+// prefill_order.h -- which workgroup of the prefill attention takes which block
+// of query positions: workgroup size, grid and order.  Host and device code, no
+// HIP header needed.
+#pragma once
+#include <stddef.h>
+
+#ifdef __HIPCC__
+#define SNAP_HD __host__ __device__ __forceinline__
+#else
+#define SNAP_HD inline
+#endif
+
+namespace snap {
+
+constexpr long kPfSmallBlocks = 1024;
+constexpr size_t kPfSpreadBytes = (size_t)64 << 20;
+
+struct PrefillOrder {
+  int waves;       // per workgroup, 32 (head, position) rows each
+  int P;           // query positions per workgroup: its rows are those of the G heads of one KV head
+  int n_qblocks;   // blocks of P positions per group, block 0 the prompt's last (the most keys)
+  int groups;      // (sequence, KV head) pairs
+  int whole;       // the first `whole` groups keep to one XCD each, the others go round all of them
+  int turn, step;  // of those: blocks after which they change places, and by how many
+  int grid;        // workgroups
+};
+
+// Group and block of a workgroup.  Consecutive workgroups go to the 8 XCDs in
+// turn.  Of the first `whole` groups, a multiple of 8, XCD x takes x, x+8, x+16,
+// ... one after the other, each from its last positions to its first, so that
+// the workgroups resident on one XCD share the same K and V tiles in its L2.
+// The other groups' blocks go round all XCDs, block by block, each group's by
+// turns to each XCD.
+// An XCD deals its workgroups out to its four shader engines in turn and in
+// order, as measured times fit: one engine that has only long ones holds up the
+// others.  Where the groups are a multiple of 32, a group is on the same engine
+// in every block unless it changes places by one XCD and one engine, 9 places
+// (by 1 place, its engine changed every 8 blocks only: 8 prompts of 512 to 4096
+// tokens with four 128-wide KV heads, longest first, 886 us a call, now 597; 691
+// with the groups on one XCD each).
+SNAP_HD void prefill_block(const PrefillOrder& o, int i, int& group, int& block) {
+  const int n_whole = o.whole * o.n_qblocks;
+  if (i < n_whole) {
+    const int r = i / 8;
+    group = r / o.n_qblocks * 8 + i % 8;
+    block = r % o.n_qblocks;
+  } else {
+    const int m = i - n_whole, mixed = o.groups - o.whole;
+    block = m / mixed;
+    group = o.whole + (m % mixed + block / o.turn * o.step) % mixed;
+  }
+}
+
+// The order of a call of n_seq prompts padded to max_len, G query heads of width
+// d per KV head.
+// Waves per workgroup.  128-wide: 8 (every tile load serves 256 rows), but 4 for
+// a call of few workgroups, whose time is that of its longest one, 64 keys a
+// turn: up to 1024 of them (one 2048-token prompt, 32 heads, 128 of them: 109 ->
+// 84 us; 8192 tokens, 512: 656 -> 644; 16384 tokens, 2048: 2187 with 8, 2229
+// with 4).  64-wide: 4, three workgroups per CU at 155 registers against one of
+// 8 waves (8 ragged prompts of up to 3000 tokens, 288 -> 187 us; 4 of up to
+// 16384, 2377 -> 2088).  More than 8 heads a group need 8 waves for a block of
+// 16 positions each.
+// Groups that do not fill the 8 XCDs evenly are spread over all of them: one KV
+// head of 16 query heads and 16384 tokens kept one XCD of eight busy (7.64 ms,
+// now 1.17).  So are all groups of a batch whose sequences' heads are not a
+// multiple of 8 (its XCDs would hold different sequences, and wait for the
+// longest), while K and V together are at most 64 MB, so that each XCD reading
+// them costs little.  839 batches of that kind, each in three orders of its
+// lengths, against groups on one XCD each: 8 groups 8% faster in the mean, 12 to
+// 48 groups 12 to 15%, 64 to 512 groups 7 to 12%; the worst 8% slower (four
+// prompts of 4096 to 16384 tokens with four 64-wide KV heads, longest first: 550
+// -> 597 us; shortest first 1.1 times faster).
+inline PrefillOrder prefill_order(int n_seq, int n_kv_heads, int G, int d, int max_len) {
+  PrefillOrder o;
+  o.groups = n_seq * n_kv_heads;
+  const long blocks8 = (long)o.groups * ((max_len + 256 / G - 1) / (256 / G));
+  o.waves = G <= 8 && (d == 64 || blocks8 <= kPfSmallBlocks) ? 4 : 8;
+  o.P = 32 * o.waves / G;
+  o.n_qblocks = (max_len + o.P - 1) / o.P;
+  const size_t kv_bytes = (size_t)o.groups * max_len * d * 4;
+  const bool spread = n_seq > 1 && n_kv_heads % 8 != 0 && kv_bytes <= kPfSpreadBytes;
+  o.whole = spread ? 0 : o.groups / 8 * 8;
+  const int mixed = o.groups - o.whole;
+  // m % 8 and m % mixed repeat together every 8 / gcd(mixed, 8) blocks
+  o.turn = mixed % 8 == 0 ? 1 : (mixed % 4 == 0 ? 2 : (mixed % 2 == 0 ? 4 : 8));
+  o.step = mixed % 32 == 0 ? 9 : 1;
+  o.grid = o.groups * o.n_qblocks;
+  return o;
+}
+
+}  // namespace snap

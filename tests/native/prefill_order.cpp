@@ -1,0 +1,18 @@
+// The prefill attention's workgroup order (csrc/prefill_order.h) for the host
+// tests: the order of a call, and every workgroup's (group, block).
+#include "prefill_order.h"
+
+extern "C" void prefill_order_of(int n_seq, int n_kv_heads, int G, int d, int max_len, int* o) {
+  const snap::PrefillOrder p = snap::prefill_order(n_seq, n_kv_heads, G, d, max_len);
+  o[0] = p.waves;
+  o[1] = p.P;
+  o[2] = p.n_qblocks;
+  o[3] = p.groups;
+  o[4] = p.whole;
+  o[5] = p.grid;
+}
+
+extern "C" void prefill_blocks_of(int n_seq, int n_kv_heads, int G, int d, int max_len, int* group, int* block) {
+  const snap::PrefillOrder p = snap::prefill_order(n_seq, n_kv_heads, G, d, max_len);
+  for (int i = 0; i < p.grid; ++i) snap::prefill_block(p, i, group[i], block[i]);
+}
