@@ -440,7 +440,7 @@ snap_status launch_prefill_attn(const snap_params& p, int n_seq, const int32_t* 
     kern = nw == 8 ? prefill_attn<4, 8> : prefill_attn<4, 4>;
   else
     kern = nw == 8 ? prefill_attn<2, 8> : prefill_attn<2, 4>;
-  hipLaunchKernelGGL(kern, dim3(pa.order.grid), dim3(64 * nw), 0, stream, pa);
+  hipLaunchKernelGGL(kern, dim3((unsigned)pa.order.grid), dim3(64 * nw), 0, stream, pa);
   if (hipGetLastError() != hipSuccess) return SNAP_ERR_HIP;
   return SNAP_OK;
 }

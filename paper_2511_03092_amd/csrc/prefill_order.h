@@ -5,14 +5,14 @@
 #include <stddef.h>
 
 #ifdef __HIPCC__
-#define SNAP_HD __host__ __device__ __forceinline__
+#define SNAP_HD __host__ __device__ inline
 #else
 #define SNAP_HD inline
 #endif
 
 namespace snap {
 
-constexpr long kPfSmallBlocks = 1024;
+constexpr long long kPfSmallBlocks = 1024;
 constexpr size_t kPfSpreadBytes = (size_t)64 << 20;
 
 struct PrefillOrder {
@@ -22,8 +22,15 @@ struct PrefillOrder {
   int groups;      // (sequence, KV head) pairs
   int whole;       // the first `whole` groups keep to one XCD each, the others go round all of them
   int turn, step;  // of those: blocks after which they change places, and by how many
-  int grid;        // workgroups
+  long long grid;  // workgroups, at most kPfMaxGrid for a call that prefill_grid_fits
 };
+
+// Largest launch grid, and the calls whose grid is within it: the groups,
+// rounded up to the 8 XCDs, in workgroups of 8 waves.
+constexpr long long kPfMaxGrid = 0x7fffffff;
+inline bool prefill_grid_fits(long long groups, int G, int max_len) {
+  return (groups + 7) / 8 * 8 * ((max_len + 256 / G - 1) / (256 / G)) <= kPfMaxGrid;
+}
 
 // Group and block of a workgroup.  Consecutive workgroups go to the 8 XCDs in
 // turn.  Of the first `whole` groups, a multiple of 8, XCD x takes x, x+8, x+16,
@@ -60,7 +67,7 @@ SNAP_HD void prefill_block(const PrefillOrder& o, int i, int& group, int& block)
 // with 4).  64-wide: 4, three workgroups per CU at 155 registers against one of
 // 8 waves (8 ragged prompts of up to 3000 tokens, 288 -> 187 us; 4 of up to
 // 16384, 2377 -> 2088).  More than 8 heads a group need 8 waves for a block of
-// 16 positions each.
+// 16 positions each, and so does a grid that 4 would take past its limit.
 // Groups that do not fill the 8 XCDs evenly are spread over all of them: one KV
 // head of 16 query heads and 16384 tokens kept one XCD of eight busy (7.64 ms,
 // now 1.17).  So are all groups of a batch whose sequences' heads are not a
@@ -74,8 +81,8 @@ SNAP_HD void prefill_block(const PrefillOrder& o, int i, int& group, int& block)
 inline PrefillOrder prefill_order(int n_seq, int n_kv_heads, int G, int d, int max_len) {
   PrefillOrder o;
   o.groups = n_seq * n_kv_heads;
-  const long blocks8 = (long)o.groups * ((max_len + 256 / G - 1) / (256 / G));
-  o.waves = G <= 8 && (d == 64 || blocks8 <= kPfSmallBlocks) ? 4 : 8;
+  auto blocks = [&](int waves) { return (long long)o.groups * ((max_len + 32 * waves / G - 1) / (32 * waves / G)); };
+  o.waves = G <= 8 && (d == 64 || blocks(8) <= kPfSmallBlocks) && blocks(4) <= kPfMaxGrid ? 4 : 8;
   o.P = 32 * o.waves / G;
   o.n_qblocks = (max_len + o.P - 1) / o.P;
   const size_t kv_bytes = (size_t)o.groups * max_len * d * 4;
@@ -85,7 +92,7 @@ inline PrefillOrder prefill_order(int n_seq, int n_kv_heads, int G, int d, int m
   // m % 8 and m % mixed repeat together every 8 / gcd(mixed, 8) blocks
   o.turn = mixed % 8 == 0 ? 1 : (mixed % 4 == 0 ? 2 : (mixed % 2 == 0 ? 4 : 8));
   o.step = mixed % 32 == 0 ? 9 : 1;
-  o.grid = o.groups * o.n_qblocks;
+  o.grid = blocks(o.waves);
   return o;
 }
 

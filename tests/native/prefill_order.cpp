@@ -2,7 +2,7 @@
 // tests: the order of a call, and every workgroup's (group, block).
 #include "prefill_order.h"
 
-extern "C" void prefill_order_of(int n_seq, int n_kv_heads, int G, int d, int max_len, int* o) {
+extern "C" void prefill_order_of(int n_seq, int n_kv_heads, int G, int d, int max_len, long long* o) {
   const snap::PrefillOrder p = snap::prefill_order(n_seq, n_kv_heads, G, d, max_len);
   o[0] = p.waves;
   o[1] = p.P;
@@ -11,6 +11,8 @@ extern "C" void prefill_order_of(int n_seq, int n_kv_heads, int G, int d, int ma
   o[4] = p.whole;
   o[5] = p.grid;
 }
+
+extern "C" bool prefill_fits(long long groups, int G, int max_len) { return snap::prefill_grid_fits(groups, G, max_len); }
 
 extern "C" void prefill_blocks_of(int n_seq, int n_kv_heads, int G, int d, int max_len, int* group, int* block) {
   const snap::PrefillOrder p = snap::prefill_order(n_seq, n_kv_heads, G, d, max_len);

@@ -24,11 +24,13 @@ def lib(tmp_path_factory):
                         os.path.join(ROOT, "tests", "native", "prefill_order.cpp"), "-o", so],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    lib.prefill_fits.argtypes, lib.prefill_fits.restype = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    return lib
 
 
 def _order(lib, *call):
-    o = (ctypes.c_int * 6)()
+    o = (ctypes.c_longlong * 6)()
     lib.prefill_order_of(*call, o)
     return SimpleNamespace(**dict(zip(("waves", "P", "n_qblocks", "groups", "whole", "grid"), o)))
 
@@ -88,3 +90,18 @@ def test_a_group_goes_round_the_engines(lib, n_seq, n_kv_heads):
     for k in range(o.n_qblocks - 7):
         counts = np.stack([(engine[:, k:k + 8] == e).sum(1) for e in range(4)])
         assert counts.min() >= 1 and counts.max() <= 3, (k, counts)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 8, 16])
+def test_largest_accepted_grids(lib, G, d):
+    """The longest prompts that a call may have: its grid, in whole numbers, is within the launch limit (a 64-wide one
+    in workgroups of half the positions would have twice that)."""
+    positions = 256 // G
+    for n_seq, n_kv_heads in ((1, 513), (8, 1024), (4096, 15), (65535, 1)):
+        groups = n_seq * n_kv_heads
+        longest = min(0x7fffffff // (-(-groups // 8) * 8) * positions, 1 << 28)
+        assert lib.prefill_fits(groups, G, longest)
+        assert longest == 1 << 28 or not lib.prefill_fits(groups, G, longest + 1)
+        o = _order(lib, n_seq, n_kv_heads, G, d, longest)
+        assert o.grid == groups * -(-longest // o.P) <= 0x7fffffff and o.P * G == 32 * o.waves, (groups, longest)
