@@ -1,9 +1,9 @@
 """snap_decode_step (append + attend for one layer in one call) against the two
 calls it replaces, snap_cache_append then snap_decode_attn: outputs and cache
 bytes must be identical bit for bit at every step, and the fused outputs match
-the fp64 oracle.  Cases cover the fused kernels (bf16 and fp8 GQA MFMA, bf16
-latent) and the two-launch one (fp32), a prompt shorter than the sinks (new
-tokens land in sink rows), the ring wrapping, and an invalid slot id.
+the fp64 oracle.  Cases cover the fused kernels (bf16 and fp8, MFMA rows of 64
+and 128 and latent) and the two-launch one (fp32), a prompt shorter than the
+sinks (new tokens land in sink rows), the ring wrapping, and an invalid slot id.
 
 Every case prints what names it before touching the GPU.
 """

@@ -119,15 +119,34 @@ def test_prefill_group_sizes(hq, hkv, d):
 @pytest.mark.parametrize("hq,hkv,d,w,recent,norm", [(8, 1, 64, 32, 16, synth.NORM_CAND),
                                                     (8, 2, 128, 64, 40, synth.NORM_ROW)])
 def test_prefill_largest_window(hq, hkv, d, w, recent, norm):
-    """The largest window (G * w = 256 score rows: exactly one attention
-    workgroup's block of 256 / G positions) with w > recent, so the causal
-    mask also cuts the candidate domain of the first window rows."""
+    """The largest window (G * w = 256 score rows) with w > recent, so the causal
+    mask also cuts the candidate domain of the first window rows.  Calls of this
+    size run workgroups of 4 waves (128 / G positions): the window spans two."""
     wl = synth.small(GQA, n_q_heads=hq, n_kv_heads=hkv, d_qk=d, d_v=d, obs_window=w, recent=recent, norm=norm)
     p = params_of(wl)
     lengths = [700, 161, 90, 50]
-    _announce(f"snap_prefill window {w} = one block of {256 // (hq // hkv)} positions, G={hq // hkv} D={d} "
+    _announce(f"snap_prefill window {w} = two blocks of {128 // (hq // hkv)} positions, G={hq // hkv} D={d} "
               f"recent={recent} norm={'cand' if norm == 0 else 'row'}: lengths {lengths}")
     _run(wl, p, lengths)
+
+
+@pytest.mark.parametrize("hq,hkv,w,recent,norm,lengths,max_len", [
+    (9, 9, 256, 40, synth.NORM_CAND, [700, 300, 255, 513], 7424),         # 36 groups: 32 on an XCD each, 4 spread
+    (10, 5, 32, 16, synth.NORM_ROW, [641, 128, 129, 1, 385], 5400),       # 25: 24 and 1
+    (8, 2, 64, 40, synth.NORM_ROW, [700, 161, 64, 50, 65], 6600),         # 10, all spread
+    (24, 3, 32, 16, synth.NORM_CAND, [515, 97, 32, 290], 2752),           # 12, all spread
+])
+def test_prefill_eight_waves(hq, hkv, w, recent, norm, lengths, max_len):
+    """Every row of the 8-wave workgroups that long 128-wide prompts run, at small
+    sizes: short prompts in a batch padded so far that it has more than 1024 of
+    their blocks (256 / G positions each).  Lengths at and beside the edges of
+    blocks and 64-key tiles; where G * w = 256 the window is one whole block."""
+    G = hq // hkv
+    assert len(lengths) * hkv * -(-max_len // (256 // G)) > 1024
+    wl = synth.small(GQA, n_q_heads=hq, n_kv_heads=hkv, obs_window=w, recent=recent, norm=norm)
+    p = params_of(wl)
+    _announce(f"snap_prefill, 8 waves: G={G} D=128 window {w} recent {recent}: lengths {lengths} padded to {max_len}")
+    _run(wl, p, lengths, max_len=max_len)
 
 
 def test_prefill_short_prompts_and_window_longer_than_prompt():

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (12, [140]),           # 8 and 4
     (6, [300, 40, 129]),   # 18 spread: turns of 4
     (2, [64, 450, 1, 200]),  # 8 spread: turns of 1
+    (4, [450, 1, 200, 64, 130, 300, 90, 513]),  # 32 spread: 9 places a turn
 ])
 def test_prefill_group_orders(hkv, lengths):
     wl = synth.small(GQA, n_q_heads=2 * hkv, n_kv_heads=hkv, d_qk=64, d_v=64, obs_window=8, recent=16, topk=40)
