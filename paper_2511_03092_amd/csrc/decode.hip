@@ -1388,10 +1388,15 @@ Geometry decode_geometry(const snap_params& p, int n) {
   // latent caches run 4-wave workgroups, the others one wave each
   const bool latent = p.v_in_k && p.d_qk == 576;
   const bool latent_lds = latent && p.kv_dtype == SNAP_BF16;  // one per CU (LDS-bound), else two
-  // 64-wide fp8 rows: 4 KB in flight per wave, so twice the waves (32 sequences
-  // x 16384 rows: 104.6 -> 93.5 us a call; 64-wide bf16 rows measured slower
-  // with them, 161.8 -> 183.5 us)
-  const bool narrow = p.d_qk == 64 && p.kv_dtype == SNAP_FP8_E4M3;
+  // 64-wide fp8 rows: 4 KB in flight per wave, so twice the waves, from 64 units
+  // on (fewer are split into short chunks anyway: 16 to 48 units x 2048 to 8192
+  // rows are up to 31% slower with them, 32 x 4096 16.8 us against 12.8).
+  // Measured against 2048 waves: 64 units x 16384 rows 38.4 -> 35.3 us, 128 57.5
+  // -> 55.6, 256 104 -> 97, 512 194 -> 176, 1024 x 8192 223 -> 177; at 2048 rows
+  // 64 units 14.2 -> 16.4 us (16 query heads each 14.9 -> 19.7), 96 15.1 ->
+  // 16.4, 192 21.0 -> 19.8, 512 41.9 -> 38.8.  64-wide bf16 rows are slower with
+  // them (256 units x 16384 rows 162 -> 184).
+  const bool narrow = p.d_qk == 64 && p.kv_dtype == SNAP_FP8_E4M3 && units >= 64;
   const int target = latent_lds ? kLatentLdsWGs : (latent ? 512 : (narrow ? 4096 : 2048));
   // rounded down: a grid just above the resident capacity would leave a
   // partial second round of workgroups (measured 25% slower on the fp8 GQA

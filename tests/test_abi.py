@@ -67,6 +67,18 @@ def test_workspace_queries_are_host_only():
     assert snap.snap_decode_workspace(_params(n_q_heads=30), 1) == 0
 
 
+@pytest.mark.parametrize("n,chunks", [(1, 128), (6, 42), (7, 36), (8, 64), (16, 32), (64, 8)])
+def test_decode_chunks_of_narrow_fp8_rows(n, chunks):
+    """64-wide fp8 caches: twice the waves of 64-wide bf16 ones from 64
+    (sequence, KV head) units on, as many below; the partials and their (max,
+    sum) pairs show the chunks per unit."""
+    align = lambda x: (x + 255) & ~255
+    size = lambda c: align(n * 32 * c * 64 * 4) + align(n * 32 * c * 8)
+    over = dict(d_qk=64, d_v=64, recent=1024, topk=3068)
+    assert snap.snap_decode_workspace(_params(kv_dtype=snap.SNAP_FP8_E4M3, **over), n) == size(chunks)
+    assert snap.snap_decode_workspace(_params(**over), n) == size(chunks if n < 8 else chunks // 2)
+
+
 def _compress_status(p, ws_bytes=1 << 30, **kw):
     L = snap.lib()
     cache = snap.SnapCache(FAKE, FAKE if not p.v_in_k else None, None, None, 4)
