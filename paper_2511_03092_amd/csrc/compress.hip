@@ -42,7 +42,6 @@ struct ScoreArgs {
   float* A;             // [n_seq*Hkv][max_len]
   int Hq, Hkv, G, w, max_len, sink, recent, norm;
   int rows, rows_pad, key_chunk, n_kchunks, groups;
-  float scale;   // softmax scale
   float scale2;     // scale * log2(e) rounded to fp32 toward zero: logits in log2 units
   float scale2_lo;  // scale * log2(e) - scale2, > 0 (see split_scale2)
 };
@@ -470,14 +469,16 @@ __global__ __launch_bounds__(NW * 64) void score_pass(ScoreArgs a) {
 }
 
 // ============================================================ streaming score passes
-// 64- and 128-wide bf16 keys.  Every wave holds all score rows of the group as
-// query fragments (RB blocks of 16 rows, RB * KS * 4 registers) and streams its
-// own blocks of 32 keys from memory into registers: no LDS and no barrier in
-// the loop, the next block in flight while one is scored.  The product is
-// S^T = K Q^T (A = 16 keys, B = 16 rows), so a lane holds one row of each block
-// against 4 * (lane / 16) + e of 16 keys: the row constants are one register
-// per block, a row's running (max, sum) is lane-local until the end, and the
-// column sums are an in-lane sum over the blocks and a reduction over 16 lanes.
+// 64- and 128-wide bf16 keys, at most 64 score rows.  Every wave holds all score
+// rows of the group as query fragments (RB blocks of 16 rows, RB * KS * 4
+// registers) and streams its own 16 keys at a time from memory into registers:
+// no LDS and no barrier in the loop, two tiles in flight while one is scored.
+// The product is S^T = K Q^T (A = 16 keys, B = 16 rows), so a lane holds one row
+// of each block against 4 * (lane / 16) + e of 16 keys: the row constants are one
+// register per block, a row's running (max, sum) is lane-local until the end, and
+// the column sums are an in-lane sum over the blocks and a reduction over 16
+// lanes.  The statistics' reference moves lazily (kStatsLag), which the LDS pass
+// gains nothing from: here it saves the rescale of every block's sums per 16 keys.
 template <int N>
 __device__ __forceinline__ float row_ror_add(float x) {
   const int r = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true);
@@ -1965,12 +1966,6 @@ static hipError_t launch_score_nw(const ScoreArgs& sa, bool colsum, int groups, 
   return hipGetLastError();
 }
 
-// Waves per workgroup: 4 while the score rows fit in 128, else 8.  Tiles and
-// stages per shape, as measured: the 576-wide latent rows take 32-key tiles in
-// 4 stages (147 KB, one workgroup per CU: three tiles in flight while one is
-// scored; 8% faster than two 64-key stages); 64/128-wide bf16 rows keep two
-// 64-key stages (three workgroups per CU; three or four stages measured
-// slower); fp32 rows 3 or 2 stages next to their fp32 query block.
 template <int KS>
 static hipError_t launch_stream(const ScoreArgs& sa, bool colsum, int groups, int n_kchunks, hipStream_t st) {
   dim3 grid(n_kchunks, groups);
@@ -1983,6 +1978,20 @@ static hipError_t launch_stream(const ScoreArgs& sa, bool colsum, int groups, in
   return hipGetLastError();
 }
 
+// Waves per workgroup: 4 while the score rows fit in 128, else 8.  Tiles and
+// stages per shape, as measured: the 576-wide latent rows take 32-key tiles in
+// 4 stages (147 KB, one workgroup per CU: three tiles in flight while one is
+// scored; 8% faster than two 64-key stages); 64/128-wide bf16 rows keep two
+// 64-key stages (three workgroups per CU; three or four stages measured
+// slower); fp32 rows 3 or 2 stages next to their fp32 query block.
+// Few rows run score_stream: whole compress calls of 1 to 16 prompts of 2000 to
+// 131072 tokens against the LDS pass, 64-wide keys, up to 32 rows 0 to 56%
+// faster (one 128k prompt 186 -> 126 us at 32 rows), 33 to 64 rows 1% slower to
+// 28% faster (16 x 128k 1107 -> 876 us); 128-wide, up to 32 rows 7% slower (a
+// short batch of one or two KV heads) to 38% faster (one 128k prompt, 8 KV heads,
+// 230 -> 178 us), 33 to 64 rows 9% slower (16 x 16k 326 -> 359 us) to 4% faster
+// (4 x 128k 447 -> 433 us).  With 128 rows a wave holds 254 registers and the
+// statistics pass of a 128k batch took 344 instead of 278 us.
 template <typename In>
 static hipError_t launch_score(const ScoreArgs& sa, int dk, bool colsum, int groups, int n_kchunks, hipStream_t st) {
   const bool wide = sa.rows_pad > 128;
@@ -2048,7 +2057,6 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
   sa.key_chunk = geo.key_chunk;
   sa.n_kchunks = geo.n_kchunks;
   sa.groups = groups;
-  sa.scale = scale;
   split_scale2(scale, sa.scale2, sa.scale2_lo);
   const bool bf = p.in_dtype == SNAP_BF16;
   hipError_t e;

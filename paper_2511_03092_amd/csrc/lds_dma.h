@@ -123,6 +123,7 @@ struct TileLoad {
     }
   }
 };
+
 // Issue this wave's share of one key tile: the tile is CPR*TK/64
 // wave-instructions, each moving 64 x 16 bytes straight into LDS (no VGPRs);
 // wave w issues instructions w, w+NW, ...  Keys past c1 read key c1-1

@@ -12,8 +12,9 @@
 // sums) instead of twice.
 //
 // Kernel sequence per call (one stream, no host synchronisation):
-//   vt_transpose   V -> V^T per (sequence, KV head): keys contiguous, zero past
-//                  the prompt (the A operand of the P V product)
+//   vt_transpose   V -> V^T per (sequence, KV head) and 64-key tile, in the bytes
+//                  of the attention's LDS tile; zero past the prompt (the A
+//                  operand of the P V product)
 //   prefill_attn   per (KV head, block of query positions): online softmax over
 //                  64-key tiles streamed into LDS, bf16 MFMA for both products;
 //                  blocks holding window rows also write their statistics and
@@ -32,7 +33,7 @@ constexpr int kPfTK = 64;  // keys per tile
 struct PrefillArgs {
   const uint16_t* q;   // [n_seq][Hq][max_len][D]
   const uint16_t* k;   // [n_seq][Hkv][max_len][D]
-  const uint16_t* vt;  // [n_seq*Hkv][D][ld_vt]
+  const uint16_t* vt;  // [n_seq*Hkv][ld_vt / 64][8][D][8] (vt_transpose)
   uint16_t* out;       // [n_seq][Hq][max_len][D]
   const int32_t* lengths;
   float2* stats;       // [n_seq*Hkv][rows_pad]: (max, sum of 2^(y - max)), y in log2 units
