@@ -27,6 +27,7 @@
 #include <math.h>
 #include <string.h>
 
+#include "band_grid.h"
 #include "lds_dma.h"
 #include "snap_internal.h"
 
@@ -2166,11 +2167,7 @@ snap_status launch_compress(const snap_params& p, const snap_cache& c, int32_t* 
     ba.rows_pad = geo.rows_pad;
     ba.n_splits = geo.n_splits;
     ba.in_f32 = !bf;
-    // workgroups per group of band_rescore, its work items strided over them:
-    // 576-wide keys (four row passes of long rows per key block) take about 1024
-    // in all (16 groups: 45 us with 16 each, 34 with 64); narrower ones 16, where
-    // more only repeat the sorting of the members (8 groups: 10.8 us, 12.9 with 64)
-    ba.band_wgs = p.d_qk <= 128 || groups >= 64 ? 16 : (groups <= 16 ? 64 : 1024 / groups);
+    ba.band_wgs = band_workgroups(p.d_qk, groups);
     // query-dim slices per score row: 8 for 576-wide bf16 rows and for fp32
     // rows, else 4 (as band_rescore dispatches)
     ba.rows_per_pass = kBandThreads / ((!bf || p.d_qk == 576) ? 8 : 4);

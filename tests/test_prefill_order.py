@@ -105,3 +105,15 @@ def test_largest_accepted_grids(lib, G, d):
         assert longest == 1 << 28 or not lib.prefill_fits(groups, G, longest + 1)
         o = _order(lib, n_seq, n_kv_heads, G, d, longest)
         assert o.grid == groups * -(-longest // o.P) <= 0x7fffffff and o.P * G == 32 * o.waves, (groups, longest)
+
+
+@pytest.mark.parametrize("groups", [1, 8, 16, 17, 31, 32, 48, 63])
+def test_rescore_groups_start_on_all_engines(lib, groups):
+    """The first workgroups of the groups' fp64 re-scores, which have the work of short latent prompts, are spread over
+    the 8 XCDs and the four shader engines of each; from 64 groups on, and for narrow keys, 16 workgroups a group."""
+    n = lib.band_workgroups_of(576, groups)
+    first = [g * n for g in range(groups)]
+    places = {(i % 8, i // 8 % 4) for i in first}
+    assert len(places) == min(groups, 32)
+    assert lib.band_workgroups_of(576, 64) == lib.band_workgroups_of(576, 1000) == 16
+    assert lib.band_workgroups_of(64, groups) == lib.band_workgroups_of(128, groups) == 16
